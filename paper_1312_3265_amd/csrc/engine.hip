@@ -713,8 +713,6 @@ void Engine::cancel(int slot, hipStream_t s) {
 }
 
 // =============================================================== Lanczos
-static constexpr int kLzBlocks = 256;
-
 size_t lanczos_workspace_bytes(const Geom& g, int formulation, int g55, int steps) {
   const int nc = ncomp_of(formulation);
   const size_t vec = (size_t)nc * g.Vp * 16;
@@ -771,9 +769,8 @@ int lanczos_run(const lq_gauge_s* gs, const lq_dirac* d, int steps, const void* 
 
   // v_1 = v0 / ||v0||
   launch_field_in(P64, nc, g, v0, 1, w, nbp, 0, 1, s);
-  launch_lz_update(g, nc, V, 0, h, w, part_n, kLzBlocks, 1, s);
-  launch_lz_finish(part_n, kLzBlocks, bd + steps, s);
-  launch_lz_normalize(g, nc, w, bd + steps, V, s);
+  launch_lz_update(g, nc, V, 0, h, w, part_n, s);
+  launch_lz_normalize(g, nc, w, part_n, bd + steps, V, s);
   check_launch();
   for (int j = 0; j < steps; ++j) {
     double2* vj = V + (size_t)j * n;
@@ -791,15 +788,16 @@ int lanczos_run(const lq_gauge_s* gs, const lq_dirac* d, int steps, const void* 
     f.vprev = (const double*)(j > 0 ? vj - n : vj);
     f.beta_prev = j > 0 ? bd + (j - 1) : nullptr;
     launch_stencil(op, P64, nl64, true, EPI_LANCZOS, oa, t, f, 1, s);
-    // w -= alpha v_j; two classical Gram-Schmidt passes against v_1..v_j
-    launch_lz_dots(g, nc, V, j + 1, w, part_a, nbp, ad + j, part_h, kLzBlocks, s);
-    launch_lz_reduce(part_h, j + 1, kLzBlocks, h, s);
-    launch_lz_update(g, nc, V, j + 1, h, w, part_n, kLzBlocks, 0, s);
-    launch_lz_dots(g, nc, V, j + 1, w, nullptr, 0, nullptr, part_h, kLzBlocks, s);
-    launch_lz_reduce(part_h, j + 1, kLzBlocks, h, s);
-    launch_lz_update(g, nc, V, j + 1, h, w, part_n, kLzBlocks, 1, s);
-    launch_lz_finish(part_n, kLzBlocks, bd + j, s);
-    if (j + 1 < steps) launch_lz_normalize(g, nc, w, bd + j, V + (size_t)(j + 1) * n, s);
+    // two classical Gram-Schmidt passes against v_1..v_j; the first takes
+    // alpha v_j out with the rest (its coefficient of v_j is alpha to rounding)
+    launch_lz_dots(g, nc, V, j + 1, w, part_h, s);
+    launch_lz_reduce(g, nc, part_h, j + 1, h, part_a, nbp, ad + j, s);
+    launch_lz_update_dots(g, nc, V, j + 1, h, w, part_h, s);
+    launch_lz_reduce(g, nc, part_h, j + 1, h, nullptr, 0, nullptr, s);
+    launch_lz_update(g, nc, V, j + 1, h, w, part_n, s);
+    // the last step needs no further vector, and its beta is not reported
+    if (j + 1 < steps)
+      launch_lz_normalize(g, nc, w, part_n, bd + j, V + (size_t)(j + 1) * n, s);
     check_launch();
   }
   std::vector<double> ha(steps), hb(steps);
@@ -883,9 +881,8 @@ int spectrum_run(const lq_gauge_s* gs, const lq_dirac* d, double sigma, int step
 
   // v_0 = v0 / ||v0||
   launch_field_in(P64, nc, g, v0, 1, w, nbp, 0, 1, s);
-  launch_lz_update(g, nc, V, 0, h, w, part_n, kLzBlocks, 1, s);
-  launch_lz_finish(part_n, kLzBlocks, bd + m, s);
-  launch_lz_normalize(g, nc, w, bd + m, V, s);
+  launch_lz_update(g, nc, V, 0, h, w, part_n, s);
+  launch_lz_normalize(g, nc, w, part_n, bd + m, V, s);
   check_launch();
   // projected matrix, (m + 1) x m: column j holds the coefficients of
   // (M - sigma)^{-1} v_j; below the kept block it stays Hessenberg
@@ -909,14 +906,15 @@ int spectrum_run(const lq_gauge_s* gs, const lq_dirac* d, double sigma, int step
                     "shift-invert solve " + std::to_string(j) + " did not converge");
       launch_field_in(P64, nc, g, cout, 1, w, nbp, 0, 1, s);
       for (int pass = 0; pass < 2; ++pass) {
-        launch_lz_dots(g, nc, V, j + 1, w, nullptr, 0, nullptr, part_h, kLzBlocks, s);
-        launch_lz_reduce(part_h, j + 1, kLzBlocks, h, s);
+        if (pass == 0) launch_lz_dots(g, nc, V, j + 1, w, part_h, s);
+        launch_lz_reduce(g, nc, part_h, j + 1, h, nullptr, 0, nullptr, s);
         LQ_HIP(hipMemcpyAsync(hh.data(), h, (size_t)(j + 1) * 16, hipMemcpyDeviceToHost, s));
-        launch_lz_update(g, nc, V, j + 1, h, w, part_n, kLzBlocks, pass == 1, s);
+        if (pass == 0) launch_lz_update_dots(g, nc, V, j + 1, h, w, part_h, s);
+        else launch_lz_update(g, nc, V, j + 1, h, w, part_n, s);
         LQ_HIP(hipStreamSynchronize(s));
         for (int r = 0; r <= j; ++r) Hat(r, j) += cplx(hh[r].x, hh[r].y);
       }
-      launch_lz_finish(part_n, kLzBlocks, bd + j, s);
+      launch_lz_finish(g, nc, part_n, bd + j, s);
       LQ_HIP(hipMemcpyAsync(&beta, bd + j, 8, hipMemcpyDeviceToHost, s));
       LQ_HIP(hipStreamSynchronize(s));
       check_launch();
@@ -929,7 +927,7 @@ int spectrum_run(const lq_gauge_s* gs, const lq_dirac* d, double sigma, int step
         break;
       }
       Hat(j + 1, j) = beta;
-      launch_lz_normalize(g, nc, w, bd + j, V + (size_t)(j + 1) * n, s);
+      launch_lz_normalize(g, nc, w, part_n, bd + j, V + (size_t)(j + 1) * n, s);
     }
     // Schur form of the projected matrix; Ritz values and estimates
     T.assign((size_t)mm * mm, cplx(0.0, 0.0));
@@ -961,7 +959,7 @@ int spectrum_run(const lq_gauge_s* gs, const lq_dirac* d, double sigma, int step
       }
       LQ_HIP(hipMemcpyAsync(h, negq.data(), (size_t)m * 16, hipMemcpyHostToDevice, s));
       launch_fill_zero(K + (size_t)q * n, vec, s);
-      launch_lz_update(g, nc, V, m, h, K + (size_t)q * n, part_n, kLzBlocks, 0, s);
+      launch_lz_update(g, nc, V, m, h, K + (size_t)q * n, nullptr, s);
       LQ_HIP(hipStreamSynchronize(s));   // h is rewritten next round
     }
     LQ_HIP(hipMemcpyAsync(V, K, vec * keep, hipMemcpyDeviceToDevice, s));

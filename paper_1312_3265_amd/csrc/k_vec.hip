@@ -1,5 +1,5 @@
-// CG vector kernels (p update, reliable updates, slot loading), the Lanczos
-// vector kernels, and the stencil launch dispatcher.
+// CG vector kernels (p update, reliable updates, slot loading) and the stencil
+// launch dispatcher.
 //
 // CG on eq. (2) per system (x0 = 0), with the low-precision vectors held in
 // units of a per-system scale s (true value = s * stored value):
@@ -380,141 +380,6 @@ void launch_load_prepare(int prec, int nc, const Geom& g, double* xhi, void* xlo
                                        dim3(kBlock), 0, s, g, (double2*)xhi,
                                        (typename XPol<PP>::type::S*)xlo, (double2*)rhi,
                                        (const double2*)b, nbp, k0, nrhs));
-}
-
-// ------------------------------------------------------------- Lanczos
-// Basis V (nvec vectors of nc*Vp complex), work vector w.  Classical
-// Gram-Schmidt: h = V^H w (lz_dots + lz_reduce), w -= V h (lz_update).
-constexpr int kDotChunk = 8;
-
-__global__ void __launch_bounds__(256)
-lz_dots_kernel(const Geom g, int nc, const double2* __restrict__ V, int nvec, double2* w,
-               const double* __restrict__ alpha_part, int nbp_alpha, double* alpha_out,
-               double* __restrict__ part_h, int nblk) {
-  __shared__ double red[16];
-  const size_t n = (size_t)nc * g.Vp;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  if (alpha_part) {
-    // w -= alpha v_j with alpha = Re<v_j, A v_j - beta v_{j-1}>, v_j = V[nvec-1]
-    const double a = sum_partials(alpha_part, nbp_alpha, red);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha_out = a;
-    const double2* vj = V + (size_t)(nvec - 1) * n;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-      double2 x = w[e];
-      x.x -= a * vj[e].x;
-      x.y -= a * vj[e].y;
-      w[e] = x;
-    }
-    __syncthreads();
-  }
-  for (int k0 = 0; k0 < nvec; k0 += kDotChunk) {
-    double re[kDotChunk], im[kDotChunk];
-#pragma unroll
-    for (int c = 0; c < kDotChunk; ++c) re[c] = im[c] = 0.0;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-      const double2 x = w[e];
-#pragma unroll
-      for (int c = 0; c < kDotChunk; ++c) {
-        if (k0 + c < nvec) {
-          const double2 v = V[(size_t)(k0 + c) * n + e];
-          re[c] += v.x * x.x + v.y * x.y;
-          im[c] += v.x * x.y - v.y * x.x;
-        }
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < kDotChunk; ++c) {
-      if (k0 + c < nvec) {
-        const double sr = block_sum(re[c], red);
-        const double si = block_sum(im[c], red);
-        if (threadIdx.x == 0) {
-          part_h[((size_t)(k0 + c) * nblk + blockIdx.x) * 2 + 0] = sr;
-          part_h[((size_t)(k0 + c) * nblk + blockIdx.x) * 2 + 1] = si;
-        }
-      }
-    }
-  }
-}
-
-__global__ void lz_reduce_kernel(const double* __restrict__ part_h, int nvec, int nblk,
-                                 double2* __restrict__ h) {
-  for (int k = threadIdx.x; k < nvec; k += blockDim.x) {
-    double sr = 0.0, si = 0.0;
-    for (int b = 0; b < nblk; ++b) {
-      sr += part_h[((size_t)k * nblk + b) * 2 + 0];
-      si += part_h[((size_t)k * nblk + b) * 2 + 1];
-    }
-    h[k] = make_double2(sr, si);
-  }
-}
-
-__global__ void __launch_bounds__(256)
-lz_update_kernel(const Geom g, int nc, const double2* __restrict__ V, int nvec,
-                 const double2* __restrict__ h, double2* w, double* __restrict__ part_n,
-                 int with_norm) {
-  __shared__ double red[16];
-  __shared__ double2 hs[1024];
-  for (int k = threadIdx.x; k < nvec && k < 1024; k += blockDim.x) hs[k] = h[k];
-  __syncthreads();
-  const size_t n = (size_t)nc * g.Vp;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  double acc = 0.0;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-    double2 x = w[e];
-    for (int k = 0; k < nvec; ++k) {
-      const double2 v = V[(size_t)k * n + e];
-      const double2 c = hs[k];
-      x.x -= v.x * c.x - v.y * c.y;
-      x.y -= v.x * c.y + v.y * c.x;
-    }
-    w[e] = x;
-    acc += x.x * x.x + x.y * x.y;
-  }
-  if (with_norm) {
-    const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) part_n[blockIdx.x] = s;
-  }
-}
-
-__global__ void lz_finish_kernel(const double* __restrict__ part_n, int nblk, double* beta_out) {
-  __shared__ double red[16];
-  const double s = sum_partials(part_n, nblk, red);
-  if (threadIdx.x == 0) *beta_out = sqrt(s);
-}
-
-__global__ void __launch_bounds__(256)
-lz_normalize_kernel(const Geom g, int nc, const double2* __restrict__ w,
-                    const double* __restrict__ beta, double2* __restrict__ vnext) {
-  const size_t n = (size_t)nc * g.Vp;
-  const double bt = *beta;
-  const double inv = (bt > 1e-300 && isfinite(bt)) ? 1.0 / bt : 0.0;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (size_t)gridDim.x * blockDim.x) {
-    const double2 x = w[e];
-    vnext[e] = make_double2(x.x * inv, x.y * inv);
-  }
-}
-
-void launch_lz_dots(const Geom& g, int nc, const double2* V, int nvec, double2* w,
-                    const double* alpha_part, int nbp_alpha, double* alpha_out, double* part_h,
-                    int nblk, hipStream_t s) {
-  hipLaunchKernelGGL(lz_dots_kernel, dim3(nblk), dim3(kBlock), 0, s, g, nc, V, nvec, w,
-                     alpha_part, nbp_alpha, alpha_out, part_h, nblk);
-}
-void launch_lz_reduce(const double* part_h, int nvec, int nblk, double2* h, hipStream_t s) {
-  hipLaunchKernelGGL(lz_reduce_kernel, dim3(1), dim3(256), 0, s, part_h, nvec, nblk, h);
-}
-void launch_lz_update(const Geom& g, int nc, const double2* V, int nvec, const double2* h,
-                      double2* w, double* part_n, int nblk, int with_norm, hipStream_t s) {
-  hipLaunchKernelGGL(lz_update_kernel, dim3(nblk), dim3(kBlock), 0, s, g, nc, V, nvec, h, w,
-                     part_n, with_norm);
-}
-void launch_lz_finish(const double* part_n, int nblk, double* beta_out, hipStream_t s) {
-  hipLaunchKernelGGL(lz_finish_kernel, dim3(1), dim3(64), 0, s, part_n, nblk, beta_out);
-}
-void launch_lz_normalize(const Geom& g, int nc, const double2* w, const double* beta,
-                         double2* vnext, hipStream_t s) {
-  hipLaunchKernelGGL(lz_normalize_kernel, dim3(1024), dim3(kBlock), 0, s, g, nc, w, beta, vnext);
 }
 
 }  // namespace lq

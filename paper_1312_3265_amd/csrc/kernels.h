@@ -84,15 +84,27 @@ int pion_blocks_per_slice(int L4);
 void launch_pion_correlator(const Geom& g, int nsrc, const double2* props, double* part,
                             double* corr, hipStream_t s);
 
-// ---- Lanczos (FP64, one vector of nc planes)
-void launch_lz_dots(const Geom& g, int nc, const double2* V, int nvec, double2* w,
-                    const double* alpha_part, int nbp_alpha, double* alpha_out, double* part_h,
-                    int nblk, hipStream_t s);
-void launch_lz_reduce(const double* part_h, int nvec, int nblk, double2* h, hipStream_t s);
+// ---- Gram-Schmidt of Lanczos and Arnoldi (FP64, vectors of nc planes)
+// Upper limit of the blocks along the vector elements, and so of the partials
+// per sum: part_h holds kLzBlocks complex numbers per vector, part_n kLzBlocks
+// doubles.
+constexpr int kLzBlocks = 512;
+// partials of h = V^H w
+void launch_lz_dots(const Geom& g, int nc, const double2* V, int nvec, double2* w, double* part_h,
+                    hipStream_t s);
+// h from its partials; alpha = the sum of alpha_part (may be null)
+void launch_lz_reduce(const Geom& g, int nc, const double* part_h, int nvec, double2* h,
+                      const double* alpha_part, int nbp_alpha, double* alpha_out, hipStream_t s);
+// w -= V h, with partials of ||w||^2 when part_n is not null
 void launch_lz_update(const Geom& g, int nc, const double2* V, int nvec, const double2* h,
-                      double2* w, double* part_n, int nblk, int with_norm, hipStream_t s);
-void launch_lz_finish(const double* part_n, int nblk, double* beta_out, hipStream_t s);
-void launch_lz_normalize(const Geom& g, int nc, const double2* w, const double* beta,
-                         double2* vnext, hipStream_t s);
+                      double2* w, double* part_n, hipStream_t s);
+// w -= V h, then the partials of V^H w
+void launch_lz_update_dots(const Geom& g, int nc, const double2* V, int nvec, const double2* h,
+                           double2* w, double* part_h, hipStream_t s);
+// beta = sqrt(sum of part_n)
+void launch_lz_finish(const Geom& g, int nc, const double* part_n, double* beta_out, hipStream_t s);
+// the same, and vnext = w / beta
+void launch_lz_normalize(const Geom& g, int nc, const double2* w, const double* part_n,
+                         double* beta_out, double2* vnext, hipStream_t s);
 
 }  // namespace lq
