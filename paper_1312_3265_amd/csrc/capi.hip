@@ -352,13 +352,17 @@ int lq_schur_apply(const lq_gauge* g, const lq_dirac* d, int32_t dagger, int32_t
   });
 }
 
+// partials per system of the timed kernels: on the lattice or its half (whose
+// site blocks may be smaller, and so more)
+static int timing_nbp(const Geom& g) { return std::max(nbp_of(g.V), nbp_of(half_geom(g).V)); }
+
 size_t lq_time_dslash_workspace_bytes(const lq_gauge* g, int32_t formulation, int32_t g55_mode,
                                       int32_t precision, int32_t nrhs) {
   if (!g || nrhs < 1 || precision < 0 || precision > 2) return 0;
   if (formulation != LQ_WILSON && formulation != LQ_STAGGERED_WILSON) return 0;
   if (g55_mode != LQ_G55_CORNERS && g55_mode != LQ_G55_ONTHEFLY) return 0;
   const size_t v = (size_t)nrhs * field_bytes(g->g, precision, ncomp_of(formulation));
-  const size_t np = (size_t)nrhs * nbp_of(g->g.V) * sizeof(double);
+  const size_t np = (size_t)nrhs * timing_nbp(g->g) * sizeof(double);
   Carver c(nullptr);
   c.take(v);
   c.take(v);
@@ -399,7 +403,7 @@ int lq_time_dslash(const lq_gauge* g, const lq_dirac* d, int32_t kernel, int32_t
            "rhs_per_thread 8 (the lanes stencil) is built for Wilson, r = 1, 18-real links, "
            "unpreconditioned");
     const size_t v = (size_t)nrhs * field_bytes(g->g, precision, nc);
-    const size_t np = (size_t)nrhs * nbp_of(g->g.V) * sizeof(double);
+    const size_t np = (size_t)nrhs * timing_nbp(g->g) * sizeof(double);
     Carver c(ws);
     void* a = c.take(v);
     void* b = c.take(v);

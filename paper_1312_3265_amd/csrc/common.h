@@ -154,6 +154,23 @@ template <class P> __host__ __device__ constexpr int field_planes(int nc) {
   return nc + (P::kSiteScale ? 1 : 0);
 }
 
+// Sites (threads) per block of the site-block kernels; partial-sum arrays hold
+// nbp_of(V) entries per right-hand side.  Fields of up to kSmallSites sites
+// are cut into blocks of one wavefront: in blocks of 256 they reach at most
+// 64 of the 256 compute units and wait for the load path of those few (the
+// line is where 64-site blocks reach every compute unit once; FP64 Wilson
+// t = M p at 8^2 x 16^2: 9.7 -> 8.5 us, nine systems 29.6 -> 26.6; at 16^4
+// 15.7 -> 16.0, 163 -> 165).
+constexpr int kSmallSites = 16384;
+constexpr int kBlockMax = 256;
+__host__ __device__ inline int block_of(int V) { return V <= kSmallSites ? 64 : kBlockMax; }
+// partials per 256 sites (sum_partials)
+__host__ __device__ inline int partials_per(int V) { return V <= kSmallSites ? 4 : 1; }
+inline int nbp_of(int V) {
+  const int block = block_of(V);
+  return ((V + block - 1) / block + 7) / 8 * 8;
+}
+
 // --------------------------------------------------------------- geometry
 // Division by a runtime-invariant 32-bit divisor via multiply-high
 // (Granlund & Montgomery, PLDI 1994): q = (umulhi(n, m) + n) >> l for n < 2^31.
@@ -440,19 +457,25 @@ __device__ __forceinline__ int phi_sign(const Coord& c) { return ((c.x[1] + c.x[
 // exact for SU(3)).  Corner matrices: eight records of 9 complex numbers.
 // RAW = true: the matrix times 1 / P::kRawScale (entries decoded without the
 // storage scale; the rebuilt row 2 brought to the same scale).
-template <class P, int NREAL, bool RAW = false>
-__device__ __forceinline__ void load_link(const typename P::S* __restrict__ u, int Vp, int mu,
-                                          int site, typename P::C m[9]) {
-  using C = typename P::C;
-  using R = typename P::R;
+// ld_link_words / dec_link: the two halves of load_link, for code that keeps
+// a link's storage words in registers until it is used.
+template <class P, int NREAL> constexpr int kLinkWords = NREAL / 2 * (int)sizeof(typename P::S) / 4;
+template <class P, int NREAL>
+__device__ __forceinline__ void ld_link_words(const typename P::S* __restrict__ u, int Vp, int mu,
+                                              int site, uint32_t w[kLinkWords<P, NREAL>]) {
   constexpr int NCX = NREAL / 2;
   // FP64 links are always stored with 18 reals (one slab per entry); the
   // 12-real FP64 variant reads only the slabs of rows 0 and 1
   constexpr int NSTORE = P::id == 0 ? 9 : NCX;
-  constexpr int BY = NCX * (int)sizeof(typename P::S);
+  ld_rec<4 * kLinkWords<P, NREAL>>(u + (size_t)mu * NSTORE * Vp, Vp, site, w);
+}
+template <class P, int NREAL, bool RAW = false>
+__device__ __forceinline__ void dec_link(const uint32_t w[kLinkWords<P, NREAL>],
+                                         typename P::C m[9]) {
+  using C = typename P::C;
+  using R = typename P::R;
+  constexpr int NCX = NREAL / 2;
   constexpr int WPC = sizeof(typename P::S) / 4;
-  uint32_t w[BY / 4];
-  ld_rec<BY>(u + (size_t)mu * NSTORE * Vp, Vp, site, w);
 #pragma unroll
   for (int k = 0; k < NCX; ++k) m[k] = RAW ? dec_raw<P>(w + k * WPC) : dec<P>(w + k * WPC);
   if constexpr (NREAL == 12) {
@@ -466,6 +489,13 @@ __device__ __forceinline__ void load_link(const typename P::S* __restrict__ u, i
     }
   }
 }
+template <class P, int NREAL, bool RAW = false>
+__device__ __forceinline__ void load_link(const typename P::S* __restrict__ u, int Vp, int mu,
+                                          int site, typename P::C m[9]) {
+  uint32_t w[kLinkWords<P, NREAL>];
+  ld_link_words<P, NREAL>(u, Vp, mu, site, w);
+  dec_link<P, NREAL, RAW>(w, m);
+}
 template <class P, int NREAL>
 __device__ __forceinline__ void store_link(typename P::S* __restrict__ u, int Vp, int mu, int site,
                                            const typename P::C m[9]) {
@@ -477,15 +507,11 @@ __device__ __forceinline__ void store_link(typename P::S* __restrict__ u, int Vp
   for (int k = 0; k < NCX; ++k) enc_to<P>(w + k * WPC, m[k]);
   st_rec<BY>(u + (size_t)mu * NCX * Vp, Vp, site, w);
 }
-template <class P, bool RAW = false>
-__device__ __forceinline__ void load_corner(const typename P::S* __restrict__ c, int Vp, int cidx,
-                                            int site, typename P::C m[9]) {
-  constexpr int BY = 9 * (int)sizeof(typename P::S);
-  constexpr int WPC = sizeof(typename P::S) / 4;
-  uint32_t w[BY / 4];
-  ld_rec<BY>(c + (size_t)cidx * 9 * Vp, Vp, site, w);
-#pragma unroll
-  for (int k = 0; k < 9; ++k) m[k] = RAW ? dec_raw<P>(w + k * WPC) : dec<P>(w + k * WPC);
+template <class P>
+__device__ __forceinline__ void ld_corner_words(const typename P::S* __restrict__ c, int Vp,
+                                                int cidx, int site,
+                                                uint32_t w[kLinkWords<P, 18>]) {
+  ld_rec<4 * kLinkWords<P, 18>>(c + (size_t)cidx * 9 * Vp, Vp, site, w);
 }
 template <class P>
 __device__ __forceinline__ void store_corner(typename P::S* __restrict__ c, int Vp, int cidx,
@@ -532,13 +558,28 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return s;
 }
 
-// Sum of n partials (one per block of an earlier launch) computed by every
-// block in the same fixed order, so every block obtains the identical value.
-__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int n, double* red) {
+// Sum of n partials of an earlier launch by one wavefront, in a fixed order, so
+// that every caller obtains the identical value.  per = 1: one partial per
+// site block of 256.  per = 4: one per 64 sites; the four of 256 sites are
+// added first, as block_sum adds the wavefronts of a block, so a sum does not
+// depend on the block size (n is a multiple of 4).
+__device__ __forceinline__ double wave_partials(const double* __restrict__ part, int n, int per) {
   double v = 0.0;
-  if (threadIdx.x < 64)
-    for (int k = threadIdx.x; k < n; k += 64) v += part[k];
-  v = (threadIdx.x < 64) ? wave_sum(v) : 0.0;
+  if (per == 4) {
+    for (int k = threadIdx.x & 63; 4 * k < n; k += 64) {
+      const double4 p = ((const double4*)part)[k];
+      v += 0.0 + p.x + p.y + p.z + p.w;
+    }
+  } else {
+    for (int k = threadIdx.x & 63; k < n; k += 64) v += part[k];
+  }
+  return wave_sum(v);
+}
+// the same, computed by every block, the value in every thread
+__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int n, double* red,
+                                               int per) {
+  double v = 0.0;
+  if (threadIdx.x < 64) v = wave_partials(part, n, per);
   __syncthreads();
   if (threadIdx.x == 0) red[0] = v;
   __syncthreads();

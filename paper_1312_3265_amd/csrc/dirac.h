@@ -544,83 +544,249 @@ __device__ __forceinline__ void dst_site(const OpArgs& a, const typename P::S* _
   }
 }
 
-// Site index and boundary sign of x + s for a diagonal offset s in {+-1}^4.
-__device__ __forceinline__ int diag_nb(const Geom& g, const Coord& c, const int s[4], int& sign) {
-  int j = 0;
-  sign = 1;
-#pragma unroll
-  for (int mu = 0; mu < 4; ++mu) {
-    int y = c.x[mu] + s[mu];
-    if (y < 0) { y += g.L[mu]; sign *= g.bc[mu]; }
-    else if (y >= g.L[mu]) { y -= g.L[mu]; sign *= g.bc[mu]; }
-    j += y * g.stride[mu];
-  }
-  return j;
-}
-
 // Corner form (K4): Gamma_55 psi(x) = phi(x) (1/16) sum_s W_s(x) psi(x+s).
 // Stored: W_s for s = (s1, s2, s3, +1), index cidx = bits (s1<0, s2<0, s3<0);
 // the s4 = -1 corners are W_{-s}(x) = W_s(x - s)^dag.
+//
+// The 24 terms of a site come in eight groups of three: group G holds the hop
+// along +-mu (mu = G / 2, backward for odd G), corner G and its reflection.
+// They are taken one after the other by one thread (site_multi) or split over
+// the wavefronts of a block (stencil_swsplit.h).  A term's storage words are
+// loaded together, before the arithmetic of the term before it where they fit
+// (kAhead): left to itself, the compiler waits for nearly every load (FP64
+// t = M p at 12^4: 32 us instead of 16).
+
+// Steps of a site to its neighbours, and the signs its terms carry (in the
+// sign bit): the eight steps with the boundary signs of the fermion field,
+// computed once for the 24 terms.
+struct SWSite {
+  int f[4], b[4];            // index steps to x + mu, x - mu
+  uint32_t fs[4], bs[4];     // boundary sign of the hop
+  uint32_t eta[4], phi;
+};
+__device__ __forceinline__ SWSite sw_site(const Geom& g, int i) {
+  const Coord c = site_coords(g, i);
+  SWSite n;
+  int par = 0;
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) {
+    const bool wf = c.x[mu] == g.L[mu] - 1, wb = c.x[mu] == 0;
+    const uint32_t flip = g.bc[mu] < 0 ? 0x80000000u : 0u;
+    n.f[mu] = wf ? (1 - g.L[mu]) * g.stride[mu] : g.stride[mu];
+    n.b[mu] = wb ? (g.L[mu] - 1) * g.stride[mu] : -g.stride[mu];
+    n.fs[mu] = wf ? flip : 0u;
+    n.bs[mu] = wb ? flip : 0u;
+    n.eta[mu] = (uint32_t)par << 31;
+    par ^= c.x[mu] & 1;
+  }
+  n.phi = (uint32_t)((c.x[1] ^ c.x[3]) & 1) << 31;
+  return n;
+}
+__device__ __forceinline__ float flip_sign(float v, uint32_t s) {
+  return __uint_as_float(__float_as_uint(v) ^ s);
+}
+__device__ __forceinline__ double flip_sign(double v, uint32_t s) {
+  return __hiloint2double((int)((uint32_t)__double2hiint(v) ^ s), __double2loint(v));
+}
+
 template <class P, int NL, bool DAG>
 struct SWCornerOp {
   using Pol = P;
   static constexpr int NC = 3;
   static constexpr int kWaves = 4;
+  static constexpr int kGroups = 8;
   using C = typename P::C;
   using R = typename P::R;
   using S = typename P::S;
+  using LP = typename LinkPol<P, NL>::type;
+  using CP = typename CornerPol<P>::type;
+
+  // the storage words of a term: its matrix and its neighbour vectors
+  static constexpr int VW = vec_rec_bytes<P>(3) / 4;
+  template <int K>
+  struct Words {
+    uint32_t m[kLinkWords<CP, 18>];
+    uint32_t v[K][VW];
+  };
+
+  // term T = 3 G + (0: hop, 1: corner, 2: reflected corner): neighbour site,
+  // its sign, whether the matrix sits there and enters adjoint
+  template <int T> static constexpr bool adjoint() {
+    return T % 3 == 0 ? (T / 3) & 1 : T % 3 == 2;
+  }
+  template <int T>
+  __device__ __forceinline__ static int neighbour(const SWSite& n, int i, uint32_t& sign) {
+    constexpr int G = T / 3, mu = G >> 1;
+    if constexpr (T % 3 == 0) {
+      sign = n.eta[mu] ^ ((G & 1) ? n.bs[mu] : n.fs[mu]);
+      return i + ((G & 1) ? n.b[mu] : n.f[mu]);
+    }
+    constexpr bool refl = T % 3 == 2;
+    sign = n.phi ^ (refl ? n.bs[3] : n.fs[3]);
+    int j = i + (refl ? n.b[3] : n.f[3]);
+#pragma unroll
+    for (int nu = 0; nu < 3; ++nu) {
+      const bool neg = ((G >> nu) & 1) != refl;
+      j += neg ? n.b[nu] : n.f[nu];
+      sign ^= neg ? n.bs[nu] : n.fs[nu];
+    }
+    return j;
+  }
+
+  template <int T, int K>
+  __device__ __forceinline__ static void load_term(const OpArgs& a, const S* __restrict__ in0,
+                                                   size_t rstride, const SWSite& n, int i,
+                                                   unsigned act, Words<K>& w) {
+    uint32_t sign;
+    const int j = neighbour<T>(n, i, sign);
+    const int jm = adjoint<T>() ? j : i;
+    if constexpr (T % 3 == 0)
+      ld_link_words<LP, NL>((const typename LP::S*)a.links, a.g.Vp, T / 6, jm, w.m);
+    else
+      ld_corner_words<CP>((const typename CP::S*)a.corners, a.g.Vp, T / 3, jm, w.m);
+    // of the systems that are not selected (or do not exist), another one's
+    // words: no branch, and the result is not used
+    const int k1 = K > 1 ? __ffs(act) - 1 : 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      ld_rec<4 * VW>(in0 + (K == 1 || ((act >> k) & 1) ? k : k1) * rstride, a.g.Vp, j, w.v[k]);
+  }
+
+  // The sums of a site and system: its hops (D_st, before the factor 1/2) and
+  // its corners (before r / 16), each in a chain of its own: the corners are an
+  // order of magnitude smaller and would be rounded at the hops' size.
+  struct Sums {
+    C hop[3], corner[3];
+  };
+  __device__ __forceinline__ static void clear(Sums& a) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a.hop[q] = a.corner[q] = czero<C>();
+  }
+
+  // y[k] = the matrix product of term T for system k, f[k] = its sign and
+  // storage scales (+-1 unless storage is 16-bit)
+  template <int T, int K>
+  __device__ __forceinline__ static void product(const SWSite& n, int i, const Words<K>& w,
+                                                 C y[K][3], R f[K]) {
+    uint32_t sign;
+    (void)neighbour<T>(n, i, sign);
+    C m[9];
+    R fm;
+    if constexpr (T % 3 == 0) {
+      // forward hops enter D_st with +eta, backward hops with -eta
+      dec_link<LP, NL, true>(w.m, m);
+      fm = (R)(adjoint<T>() ? -1 : 1) * (R)LP::kRawScale;
+    } else {
+      dec_link<CP, 18, true>(w.m, m);
+      fm = (R)CP::kRawScale;
+    }
+    fm = flip_sign(fm, sign);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      C v[3];
+      R sc;
+      dec_site_raw<P, 3>(w.v[k], v, sc);
+      if constexpr (adjoint<T>()) mvd(m, v, y[k]); else mv(m, v, y[k]);
+      f[k] = fm * sc;
+    }
+  }
+
+  // terms T0 ... T1 - 1 added to acc
+  // (FP64: one term's words are 48 registers; with two terms in flight three
+  // waves fit on a SIMD and t = M p at 16^3 x 32 takes 136 us instead of 55)
+  static constexpr int kAhead = P::id == 0 ? 0 : 1;
+  template <int T0, int T1, int K, int T = T0 - kAhead>
+  __device__ __forceinline__ static void terms(const OpArgs& a, const S* __restrict__ in0,
+                                               size_t rstride, const SWSite& n, int i,
+                                               unsigned act, Words<K>* w, Sums acc[K]) {
+    if constexpr (T < T1) {
+      constexpr int L = T + kAhead;
+      if constexpr (L < T1)
+        load_term<L, K>(a, in0, rstride, n, i, act, w[L % (kAhead + 1)]);
+      if constexpr (T >= T0) {
+        __builtin_amdgcn_sched_barrier(0);
+        C y[K][3];
+        R f[K];
+        product<T, K>(n, i, w[T % (kAhead + 1)], y, f);
+        // the sums are pinned between the loads before and after them
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          C* s = T % 3 == 0 ? acc[k].hop : acc[k].corner;
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            // scaled, then added, as the split form does; a factor of +-1 may
+            // be fused (the product is exact)
+            if constexpr (P::kSiteScale) s[q] = cadd(s[q], cscale(y[k][q], f[k]));
+            else s[q] = cfmas(y[k][q], f[k], s[q]);
+            asm volatile("" : "+v"(s[q].x), "+v"(s[q].y)::"memory");
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      terms<T0, T1, K, T + 1>(a, in0, rstride, n, i, act, w, acc);
+    }
+  }
+
+  // M psi (M^dag psi) at the site: (m + r) psi(x) + D_st / 2 - r Gamma_55
+  __device__ __forceinline__ static void finish(const OpArgs& a, const S* __restrict__ in, int i,
+                                                int k, const Sums& s, C out[3]) {
+    const R mr = (R)(rhs_mass(a, k) + a.r);
+    const R dcoef = DAG ? (R)-0.5 : (R)0.5, gcoef = (R)(a.r / 16.0);
+    C v[3];
+    ld_site<P, 3>(in, a.g.Vp, i, v);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      out[q] = csub(cadd(cscale(v[q], mr), cscale(s.hop[q], dcoef)), cscale(s.corner[q], gcoef));
+  }
+
+  // y = the term T of one system
+  template <int T>
+  __device__ __forceinline__ static void term(const SWSite& n, int i, const Words<1>& w, C y[3]) {
+    C z[1][3];
+    R f[1];
+    product<T, 1>(n, i, w, z, f);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      y[q] = cscale(z[0][q], f[0]);
+      if constexpr (P::id == 0) asm volatile("" : "+v"(y[q].x), "+v"(y[q].y)::"memory");
+    }
+    if constexpr (P::id == 0) __builtin_amdgcn_sched_barrier(0);
+  }
+  // the three terms of group r (uniform over the wavefront)
+  template <int G = 0>
+  __device__ __forceinline__ static void group_terms(const OpArgs& a, const S* __restrict__ in,
+                                                     const SWSite& n, int i, int r, C y[3][3]) {
+    if constexpr (G < kGroups) {
+      if (r == G) {
+        Words<1> w[3];
+        load_term<3 * G, 1>(a, in, 0, n, i, 1u, w[0]);
+        if constexpr (P::id != 0) {   // all three in flight; FP64 would spill
+          load_term<3 * G + 1, 1>(a, in, 0, n, i, 1u, w[1]);
+          load_term<3 * G + 2, 1>(a, in, 0, n, i, 1u, w[2]);
+        }
+        term<3 * G>(n, i, w[0], y[0]);
+        if constexpr (P::id == 0) load_term<3 * G + 1, 1>(a, in, 0, n, i, 1u, w[1]);
+        term<3 * G + 1>(n, i, w[1], y[1]);
+        if constexpr (P::id == 0) load_term<3 * G + 2, 1>(a, in, 0, n, i, 1u, w[2]);
+        term<3 * G + 2>(n, i, w[2], y[2]);
+      }
+      group_terms<G + 1>(a, in, n, i, r, y);
+    }
+  }
 
   template <int K>
   __device__ __forceinline__ static void site_multi(const OpArgs& a, const S* __restrict__ in0,
                                                     size_t rstride, int i, int k0, unsigned act,
                                                     C out[K][3]) {
-    const Geom& g = a.g;
-    Coord c = site_coords(g, i);
-    C d[K][3];
-    dst_site<P, NL, K>(a, in0, rstride, c, i, act, d);
-    C acc[K][3];
+    const SWSite n = sw_site(a.g, i);
+    Sums acc[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) clear(acc[k]);
+    Words<K> w[kAhead + 1];
+    terms<0, 3 * kGroups, K>(a, in0, rstride, n, i, act, w, acc);
 #pragma unroll
     for (int k = 0; k < K; ++k)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) acc[k][q] = czero<C>();
-    using CP = typename CornerPol<P>::type;
-    const typename CP::S* W = (const typename CP::S*)a.corners;
-#pragma unroll 1
-    for (int h = 0; h < 16; ++h) {
-      // h = 2*cidx + reflected: forward corner W_s(x) psi(x + s), or the
-      // reflected one W_{-s}(x) psi(x - s) = W_s(x - s)^dag psi(x - s)
-      const int cidx = h >> 1;
-      const bool refl = h & 1;
-      const int sg4 = refl ? -1 : 1;
-      int s[4] = {(cidx & 1) ? -sg4 : sg4, (cidx & 2) ? -sg4 : sg4, (cidx & 4) ? -sg4 : sg4, sg4};
-      int sign;
-      const int j = diag_nb(g, c, s, sign);
-      C w[9];
-      load_corner<CP, true>(W, g.Vp, cidx, refl ? j : i, w);   // raw: scale joins below
-      const R sgc = (R)sign * (R)CP::kRawScale;
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        if (!((act >> k) & 1)) continue;
-        C v[3], y[3];
-        R sc;
-        ld_site_raw<P, 3>(in0 + k * rstride, g.Vp, j, v, sc);
-        if (refl) mvd(w, v, y); else mv(w, v, y);
-        const R f = sgc * sc;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) acc[k][q] = cadd(acc[k][q], cscale(y[q], f));
-      }
-    }
-    const R gcoef = (R)(a.r * phi_sign(c) / 16.0);
-    const R dcoef = DAG ? (R)-0.5 : (R)0.5;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const R mr = (R)(rhs_mass(a, k0 + k) + a.r);
-      C v[3] = {czero<C>(), czero<C>(), czero<C>()};
-      if ((act >> k) & 1) ld_site<P, 3>(in0 + k * rstride, g.Vp, i, v);
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        out[k][q] = csub(cadd(cscale(v[q], mr), cscale(d[k][q], dcoef)), cscale(acc[k][q], gcoef));
-    }
+      if ((act >> k) & 1) finish(a, in0 + k * rstride, i, k0 + k, acc[k], out[k]);
   }
 };
 

@@ -160,7 +160,7 @@ std::string tune_key(const Geom& g, int op, int prec, int nl, int nslots) {
   LQ_HIP(hipGetDevice(&dev));
   LQ_HIP(hipGetDeviceProperties(&prop, dev));
   std::ostringstream key;
-  key << "v13:" << prop.gcnArchName << ":" << g.L[0] << "x" << g.L[1] << "x" << g.L[2] << "x" << g.L[3]
+  key << "v14:" << prop.gcnArchName << ":" << g.L[0] << "x" << g.L[1] << "x" << g.L[2] << "x" << g.L[3]
       << ":op" << op << ":p" << prec << ":l" << nl << ":n" << nslots;
   std::string k = key.str();
   for (auto& ch : k) if (ch == ' ') ch = '_';
@@ -510,11 +510,11 @@ void Engine::load(int slot, const void* chi, double mass, double tol, int maxite
   launch_load_prepare(prec_lo, nc, g, (double*)xhi, xlo, (double*)rhi, (const double*)b, nbp, slot,
                       1, s);
   const double ncomp = (double)nc * g.V;
-  launch_ru_finish(st, nullptr, part_u, eo ? part_f : nullptr, eo ? part_g : nullptr, nbp, slot, 1,
-                   ncomp, prec_lo != P64, max_cand, 1, 0, s);
+  launch_ru_finish(st, nullptr, part_u, eo ? part_f : nullptr, eo ? part_g : nullptr, nbp,
+                   partials_per(g.V), slot, 1, ncomp, prec_lo != P64, max_cand, 1, 0, s);
   launch_ru_convert(prec_lo, nc, g, st, nullptr, (const double*)rhi, rlo, ring(), part_u, nbp, 1, slot,
                     1, s);
-  launch_ru_commit(st, nullptr, part_u, nbp, slot, 1, s);
+  launch_ru_commit(st, nullptr, part_u, nbp, partials_per(g.V), slot, 1, s);
   check_launch();
   LQ_HIP(hipMemcpyAsync(hst + slot, st + slot, sizeof(SlotState), hipMemcpyDeviceToHost, s));
   LQ_HIP(hipStreamSynchronize(s));
@@ -584,11 +584,11 @@ void Engine::enqueue_reliable_update(hipStream_t s) {
     f.b = b;
     stencil(P64, nl64, true, EPI_RESID, t64, f, nslots, s);
   }
-  launch_ru_finish(st, mask, part_u, eo ? part_f : nullptr, eo ? part_g : nullptr, nbp, 0, nslots,
-                   (double)nc * g.V, prec_lo != P64, max_cand, 0, 0, s);
+  launch_ru_finish(st, mask, part_u, eo ? part_f : nullptr, eo ? part_g : nullptr, nbp,
+                   partials_per(g.V), 0, nslots, (double)nc * g.V, prec_lo != P64, max_cand, 0, 0, s);
   launch_ru_convert(prec_lo, nc, g, st, mask, (const double*)rhi, rlo, ring(), part_u, nbp, 0, 0, nslots,
                     s);
-  launch_ru_commit(st, mask, part_u, nbp, 0, nslots, s);
+  launch_ru_commit(st, mask, part_u, nbp, partials_per(g.V), 0, nslots, s);
   check_launch();
 }
 

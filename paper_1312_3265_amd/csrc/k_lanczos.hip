@@ -198,11 +198,12 @@ lz_update_kernel(const double2* __restrict__ V, size_t n, int nvec, const double
 // not null): alpha = the sum of the Lanczos stencil's partials.
 __global__ void __launch_bounds__(64)
 lz_reduce_kernel(const double* __restrict__ part_h, int nvec, int nblk, double2* __restrict__ h,
-                 const double* __restrict__ alpha_part, int nbp_alpha, double* alpha_out) {
+                 const double* __restrict__ alpha_part, int nbp_alpha, int per_alpha,
+                 double* alpha_out) {
   __shared__ double red[16];
   const int k = blockIdx.x;
   if (k == nvec) {
-    const double a = sum_partials(alpha_part, nbp_alpha, red);
+    const double a = sum_partials(alpha_part, nbp_alpha, red, per_alpha);
     if (threadIdx.x == 0) *alpha_out = a;
     return;
   }
@@ -219,7 +220,7 @@ lz_reduce_kernel(const double* __restrict__ part_h, int nvec, int nblk, double2*
 
 __global__ void lz_finish_kernel(const double* __restrict__ part_n, int nblk, double* beta_out) {
   __shared__ double red[16];
-  const double s = sum_partials(part_n, nblk, red);
+  const double s = sum_partials(part_n, nblk, red, 1);
   if (threadIdx.x == 0) *beta_out = sqrt(s);
 }
 
@@ -229,7 +230,7 @@ __global__ void __launch_bounds__(256)
 lz_normalize_kernel(size_t n, const double2* __restrict__ w, const double* __restrict__ part_n,
                     int nblk, double* beta_out, double2* __restrict__ vnext) {
   __shared__ double red[16];
-  const double bt = sqrt(sum_partials(part_n, nblk, red));
+  const double bt = sqrt(sum_partials(part_n, nblk, red, 1));
   if (blockIdx.x == 0 && threadIdx.x == 0) *beta_out = bt;
   const double inv = (bt > 1e-300 && isfinite(bt)) ? 1.0 / bt : 0.0;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
@@ -265,7 +266,7 @@ void launch_lz_reduce(const Geom& g, int nc, const double* part_h, int nvec, dou
                       const double* alpha_part, int nbp_alpha, double* alpha_out, hipStream_t s) {
   const int nb = lz_blocks((size_t)nc * g.Vp);
   hipLaunchKernelGGL(lz_reduce_kernel, dim3(nvec + (alpha_part ? 1 : 0)), dim3(64), 0, s, part_h,
-                     nvec, nb, h, alpha_part, nbp_alpha, alpha_out);
+                     nvec, nb, h, alpha_part, nbp_alpha, partials_per(g.V), alpha_out);
 }
 
 void launch_lz_update(const Geom& g, int nc, const double2* V, int nvec, const double2* h,

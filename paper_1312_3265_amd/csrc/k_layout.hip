@@ -81,11 +81,11 @@ field_out_kernel(const Geom g, const typename P::S* __restrict__ soa, void* __re
   do {                                                                                    \
     if (par < 0)                                                                          \
       LQ_PNC(prec, nc, hipLaunchKernelGGL((KERNEL<PP, NCC, F64FLAG, false>),              \
-                                          dim3(nbp * nrhs), dim3(kBlock), 0, s, g, SRC, DST, \
+                                          dim3(nbp * nrhs), dim3(block_of(g.V)), 0, s, g, SRC, DST, \
                                           par, nbp, k0, nrhs));                           \
     else                                                                                  \
       LQ_PNC(prec, nc, hipLaunchKernelGGL((KERNEL<PP, NCC, F64FLAG, true>),               \
-                                          dim3(nbp * nrhs), dim3(kBlock), 0, s, g, SRC, DST, \
+                                          dim3(nbp * nrhs), dim3(block_of(g.V)), 0, s, g, SRC, DST, \
                                           par, nbp, k0, nrhs));                           \
   } while (0)
 
@@ -374,7 +374,7 @@ plaquette_kernel(const Geom g, const double2* __restrict__ u, double* __restrict
 __global__ void plaquette_finish_kernel(const double* __restrict__ part, int n, double V,
                                         double* out) {
   __shared__ double red[16];
-  const double s = sum_partials(part, n, red);
+  const double s = sum_partials(part, n, red, 1);
   if (threadIdx.x == 0) *out = s / (6.0 * V);
 }
 
@@ -479,7 +479,7 @@ void launch_fill_test(int prec, int nc, const Geom& g, void* soa, int nrhs, uint
                       hipStream_t s) {
   const int nbp = nbp_of(g.V);
   if (nbp * nrhs == 0) return;
-  LQ_PNC(prec, nc, hipLaunchKernelGGL((fill_test_kernel<PP, NCC>), dim3(nbp * nrhs), dim3(256), 0,
+  LQ_PNC(prec, nc, hipLaunchKernelGGL((fill_test_kernel<PP, NCC>), dim3(nbp * nrhs), dim3(block_of(g.V)), 0,
                                       s, g, (typename PP::S*)soa, nbp, nrhs, seed));
 }
 

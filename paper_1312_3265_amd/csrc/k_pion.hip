@@ -34,7 +34,7 @@ pion_partial_kernel(const double2* __restrict__ props, int nsrc, long long V, lo
 __global__ void __launch_bounds__(64)
 pion_finish_kernel(const double* __restrict__ part, int B, double* __restrict__ corr) {
   __shared__ double red[16];
-  const double s = sum_partials(part + (size_t)blockIdx.x * B, B, red);
+  const double s = sum_partials(part + (size_t)blockIdx.x * B, B, red, 1);
   if (threadIdx.x == 0) corr[blockIdx.x] = s;
 }
 

@@ -137,9 +137,10 @@ static void launch_levels(const OpArgs& oa, const void* in, const EpiArgs& ea, i
   const int grid = ea.nbp * nrhs;
   if (grid == 0) return;
   const auto* x = (const typename P::S*)in;
-  hipLaunchKernelGGL((g55_level_kernel<P, NL, 1>), dim3(grid), dim3(kBlock), 0, s, oa, x, ea, nrhs);
-  hipLaunchKernelGGL((g55_level_kernel<P, NL, 2>), dim3(grid), dim3(kBlock), 0, s, oa, x, ea, nrhs);
-  hipLaunchKernelGGL((g55_level_kernel<P, NL, 3>), dim3(grid), dim3(kBlock), 0, s, oa, x, ea, nrhs);
+  const dim3 blk(block_of(oa.g.V));
+  hipLaunchKernelGGL((g55_level_kernel<P, NL, 1>), dim3(grid), blk, 0, s, oa, x, ea, nrhs);
+  hipLaunchKernelGGL((g55_level_kernel<P, NL, 2>), dim3(grid), blk, 0, s, oa, x, ea, nrhs);
+  hipLaunchKernelGGL((g55_level_kernel<P, NL, 3>), dim3(grid), blk, 0, s, oa, x, ea, nrhs);
 }
 
 void launch_stencil_otf(int prec, int nl, bool dag, int epi, const OpArgs& oa, const void* in,

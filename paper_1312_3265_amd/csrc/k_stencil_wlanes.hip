@@ -14,18 +14,20 @@ static void launch_lanes(const OpArgs& oa, const void* in, const EpiArgs& ea, in
                          hipStream_t s) {
   using Op = WilsonLanesOp<P, 18, DAG>;
   const int ngroups = (nrhs + 3) / 4;
-  const int grid = ea.nbp * ngroups;
+  const int nb = ((oa.g.V + kBlockMax - 1) / kBlockMax + 7) / 8 * 8;
+  const int chunked = block_of(oa.g.V) == 64;
+  const int grid = nb * ngroups;
   if (grid == 0) return;
   const auto* x = (const typename Op::S*)in;
   if constexpr (EPI == EPI_CG_UPDATE) {
     if (ea.stream) {
       hipLaunchKernelGGL((stencil_lanes_kernel<Op, EPI, kStream>), dim3(grid), dim3(kLanesBlock),
-                         0, s, oa, x, ea, ngroups, nrhs);
+                         0, s, oa, x, ea, nb, chunked, ngroups, nrhs);
       return;
     }
   }
   hipLaunchKernelGGL((stencil_lanes_kernel<Op, EPI, 0>), dim3(grid), dim3(kLanesBlock), 0, s, oa,
-                     x, ea, ngroups, nrhs);
+                     x, ea, nb, chunked, ngroups, nrhs);
 }
 
 template <class P>

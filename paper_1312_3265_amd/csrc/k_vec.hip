@@ -65,7 +65,7 @@ p_update_kernel(const Geom g, SlotState* st, int par, int pend_next, const doubl
     }
     return;
   }
-  const double rr = sum_partials(part + (size_t)k * nbp, nbp, red);
+  const double rr = sum_partials(part + (size_t)k * nbp, nbp, red, partials_per(g.V));
   const double rho = s->rho[par];
   const double beta = (rho > 0.0 && isfinite(rr)) ? rr / rho : 0.0;
   const int i = sb * blockDim.x + threadIdx.x;
@@ -162,18 +162,18 @@ ru_accumulate_kernel(const Geom g, const SlotState* st, const int* mask, double2
 // not met the Schur system's target is lowered in proportion.
 __global__ void ru_finish_kernel(SlotState* st, const int* mask, const double* __restrict__ part,
                                  const double* __restrict__ part_f,
-                                 const double* __restrict__ part_g, int nbp, int k0, double ncomp,
-                                 int rescale, int max_cand, int init, int par) {
+                                 const double* __restrict__ part_g, int nbp, int per, int k0,
+                                 double ncomp, int rescale, int max_cand, int init, int par) {
   __shared__ double red[16];
   const int k = k0 + blockIdx.x;
   SlotState* s = st + k;
   if (!ru_selected(st, mask, k)) return;
-  const double rr = sum_partials(part + (size_t)k * nbp, nbp, red);
+  const double rr = sum_partials(part + (size_t)k * nbp, nbp, red, per);
   const bool eo = part_f != nullptr;
   double f2 = 0.0, g2 = 0.0;
   if (eo) {
-    f2 = sum_partials(part_f + (size_t)k * nbp, nbp, red);
-    g2 = sum_partials(part_g + (size_t)k * nbp, nbp, red);
+    f2 = sum_partials(part_f + (size_t)k * nbp, nbp, red, per);
+    g2 = sum_partials(part_g + (size_t)k * nbp, nbp, red, per);
   }
   if (threadIdx.x != 0) return;
   if (init) {
@@ -277,12 +277,12 @@ ru_convert_kernel(const Geom g, const SlotState* st, const int* mask,
 }
 
 __global__ void ru_commit_kernel(SlotState* st, const int* mask, const double* __restrict__ part,
-                                 int nbp, int k0) {
+                                 int nbp, int per, int k0) {
   __shared__ double red[16];
   const int k = k0 + blockIdx.x;
   SlotState* s = st + k;
   if (!ru_selected(st, mask, k)) return;
-  const double rr = sum_partials(part + (size_t)k * nbp, nbp, red);
+  const double rr = sum_partials(part + (size_t)k * nbp, nbp, red, per);
   if (threadIdx.x != 0) return;
   s->rho[0] = s->rho[1] = rr;
   s->rho_ru = rr;
@@ -333,7 +333,7 @@ void launch_p_update(int prec, int nc, const Geom& g, SlotState* st, int par, in
                      int nrhs, hipStream_t s) {
   if (nbp * nrhs == 0) return;
   LQ_PREC_NC_SWITCH(prec, nc,
-                    hipLaunchKernelGGL((p_update_kernel<PP, NCC>), dim3(nbp * nrhs), dim3(kBlock),
+                    hipLaunchKernelGGL((p_update_kernel<PP, NCC>), dim3(nbp * nrhs), dim3(block_of(g.V)),
                                        0, s, g, st, par, pend_next, part, nbp, (const typename PP::S*)p,
                                        (typename PP::S*)pout, (const typename PP::S*)r, k0, nrhs));
 }
@@ -344,16 +344,16 @@ void launch_ru_accumulate(int prec, int nc, const Geom& g, const SlotState* st, 
   if (nbp * nrhs == 0) return;
   LQ_PREC_NC_SWITCH(prec, nc,
                     hipLaunchKernelGGL((ru_accumulate_kernel<PP, NCC>), dim3(nbp * nrhs),
-                                       dim3(kBlock), 0, s, g, st, mask, (double2*)xhi,
+                                       dim3(block_of(g.V)), 0, s, g, st, mask, (double2*)xhi,
                                        (typename XPol<PP>::type::S*)xlo, ring, nbp, k0, nrhs));
 }
 
 void launch_ru_finish(SlotState* st, const int* mask, const double* part, const double* part_f,
-                      const double* part_g, int nbp, int k0, int nrhs, double ncomp, int rescale,
-                      int max_cand, int init, int par, hipStream_t s) {
+                      const double* part_g, int nbp, int per, int k0, int nrhs, double ncomp,
+                      int rescale, int max_cand, int init, int par, hipStream_t s) {
   if (nrhs == 0) return;
   hipLaunchKernelGGL(ru_finish_kernel, dim3(nrhs), dim3(64), 0, s, st, mask, part, part_f, part_g,
-                     nbp, k0, ncomp, rescale, max_cand, init, par);
+                     nbp, per, k0, ncomp, rescale, max_cand, init, par);
 }
 
 void launch_ru_convert(int prec, int nc, const Geom& g, const SlotState* st, const int* mask,
@@ -362,14 +362,14 @@ void launch_ru_convert(int prec, int nc, const Geom& g, const SlotState* st, con
   if (nbp * nrhs == 0) return;
   LQ_PREC_NC_SWITCH(prec, nc,
                     hipLaunchKernelGGL((ru_convert_kernel<PP, NCC>), dim3(nbp * nrhs),
-                                       dim3(kBlock), 0, s, g, st, mask, (const double2*)rhi,
+                                       dim3(block_of(g.V)), 0, s, g, st, mask, (const double2*)rhi,
                                        (typename PP::S*)rlo, ring, part, nbp, init, k0, nrhs));
 }
 
-void launch_ru_commit(SlotState* st, const int* mask, const double* part, int nbp, int k0,
-                      int nrhs, hipStream_t s) {
+void launch_ru_commit(SlotState* st, const int* mask, const double* part, int nbp, int per,
+                      int k0, int nrhs, hipStream_t s) {
   if (nrhs == 0) return;
-  hipLaunchKernelGGL(ru_commit_kernel, dim3(nrhs), dim3(64), 0, s, st, mask, part, nbp, k0);
+  hipLaunchKernelGGL(ru_commit_kernel, dim3(nrhs), dim3(64), 0, s, st, mask, part, nbp, per, k0);
 }
 
 void launch_load_prepare(int prec, int nc, const Geom& g, double* xhi, void* xlo, double* rhi,
@@ -377,7 +377,7 @@ void launch_load_prepare(int prec, int nc, const Geom& g, double* xhi, void* xlo
   if (nbp * nrhs == 0) return;
   LQ_PREC_NC_SWITCH(prec, nc,
                     hipLaunchKernelGGL((load_prepare_kernel<PP, NCC>), dim3(nbp * nrhs),
-                                       dim3(kBlock), 0, s, g, (double2*)xhi,
+                                       dim3(block_of(g.V)), 0, s, g, (double2*)xhi,
                                        (typename XPol<PP>::type::S*)xlo, (double2*)rhi,
                                        (const double2*)b, nbp, k0, nrhs));
 }

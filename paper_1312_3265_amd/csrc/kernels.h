@@ -18,11 +18,6 @@ struct PRing {
   void* p[4];
 };
 
-// Threads per block of every site-block kernel; partial-sum arrays hold
-// nbp(V) entries per right-hand side.
-constexpr int kBlock = 256;
-inline int nbp_of(int V, int block = kBlock) { return (((V + block - 1) / block) + 7) / 8 * 8; }
-
 // ---- stencils: op = OpKind, prec = Prec, nl = 18/12 link reals
 void launch_stencil(int op, int prec, int nl, bool dag, int epi, const OpArgs& oa,
                     const void* in, const EpiArgs& ea, int nrhs, hipStream_t s);
@@ -39,15 +34,16 @@ void launch_p_update(int prec, int nc, const Geom& g, SlotState* st, int par, in
 void launch_ru_accumulate(int prec, int nc, const Geom& g, const SlotState* st, const int* mask,
                           double* xhi, void* xlo, const PRing& ring, int nbp, int k0, int nrhs,
                           hipStream_t s);
-// part_f, part_g: the even-odd norms (null otherwise), see ru_finish_kernel
+// part_f, part_g: the even-odd norms (null otherwise), see ru_finish_kernel;
+// per: partials_per of the fields
 void launch_ru_finish(SlotState* st, const int* mask, const double* part, const double* part_f,
-                      const double* part_g, int nbp, int k0, int nrhs, double ncomp, int rescale,
-                      int max_cand, int init, int par, hipStream_t s);
+                      const double* part_g, int nbp, int per, int k0, int nrhs, double ncomp,
+                      int rescale, int max_cand, int init, int par, hipStream_t s);
 void launch_ru_convert(int prec, int nc, const Geom& g, const SlotState* st, const int* mask,
                        const double* rhi, void* rlo, const PRing& ring, double* part, int nbp,
                        int init, int k0, int nrhs, hipStream_t s);
-void launch_ru_commit(SlotState* st, const int* mask, const double* part, int nbp, int k0,
-                      int nrhs, hipStream_t s);
+void launch_ru_commit(SlotState* st, const int* mask, const double* part, int nbp, int per,
+                      int k0, int nrhs, hipStream_t s);
 void launch_load_prepare(int prec, int nc, const Geom& g, double* xhi, void* xlo, double* rhi,
                          const double* b, int nbp, int k0, int nrhs, hipStream_t s);
 

@@ -140,13 +140,13 @@ __device__ __forceinline__ bool slot_active(const SlotState* st, int k, int mode
 // Register budget: FP64 kernels are held to 3-4 waves per SIMD so that enough
 // waves are resident to cover HBM latency.
 //
-// K systems per thread: the block covers kBlock sites of the K systems
+// K systems per thread: the block covers blockDim.x sites of the K systems
 // k0 .. k0+K-1 (k0 = ea.k0 + K * group); links and corner matrices are loaded
 // once per site for all K.  Each system keeps its own alpha, state and
 // partial sums, so the result of a system does not depend on K or on the
 // other systems.
 template <class Op, int K>
-constexpr int stencil_waves() { return (Op::NC == 12 && K >= 2) ? 3 : Op::kWaves; }
+constexpr int stencil_waves() { return (Op::NC == 12 ? K >= 2 : K >= 4) ? 3 : Op::kWaves; }
 
 // CG_UPDATE at one site for system k (offset off into the batched fields):
 // r -= alpha q with ||r||^2 returned, and on the last iteration of a group of
@@ -216,61 +216,66 @@ __device__ __forceinline__ double cg_update_site(const EpiArgs& ea, int Vp, int 
   return n2;
 }
 
-// The epilogue of one site for the K systems of a thread (see the header of
-// this file), with the block partial of the site block sb.  Every thread of
-// the block must call it (block_sum synchronises the block).
+// The epilogue of one site for system k (see the header of this file): stores
+// what the epilogue stores and returns the site's share of its block partial.
+template <class Op, int EPI, int CP>
+__device__ __forceinline__ double site_finish(const OpArgs& oa, const EpiArgs& ea, int k, int i,
+                                              const typename Op::C o[Op::NC], double alpha) {
+  using S = typename Op::S;
+  constexpr int NC = Op::NC;
+  const int Vp = oa.g.Vp;
+  const size_t off = (size_t)k * field_planes<typename Op::Pol>(NC) * Vp;
+  double acc = 0.0;
+  if constexpr (EPI == EPI_STORE || EPI == EPI_STORE_NORM) {
+    const double n2 = st_site<typename Op::Pol, NC>((S*)ea.out + off, Vp, i, o);
+    if constexpr (EPI == EPI_STORE_NORM) acc = n2;
+  } else if constexpr (EPI == EPI_CG_UPDATE) {
+    acc = cg_update_site<Op, CP>(ea, Vp, k, off, i, alpha, o);
+  } else if constexpr (EPI == EPI_RESID) {
+    double2* out = (double2*)ea.out + off;
+    const double2* b = (const double2*)ea.b + off;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const size_t e = (size_t)q * Vp + i;
+      double2 bv = b[e];
+      double2 w;
+      w.x = bv.x - (double)o[q].x;
+      w.y = bv.y - (double)o[q].y;
+      out[e] = w;
+      acc += w.x * w.x + w.y * w.y;
+    }
+  } else if constexpr (EPI == EPI_LANCZOS) {
+    double2* out = (double2*)ea.out + off;
+    const double2* v = (const double2*)ea.v + off;
+    const double2* vp = (const double2*)ea.vprev + off;
+    const double bp = ea.beta_prev ? *ea.beta_prev : 0.0;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const size_t e = (size_t)q * Vp + i;
+      double2 w;
+      w.x = (double)o[q].x - bp * vp[e].x;
+      w.y = (double)o[q].y - bp * vp[e].y;
+      out[e] = w;
+      acc += v[e].x * w.x + v[e].y * w.y;
+    }
+  }
+  return acc;
+}
+
+// site_finish for the K systems of a thread, with the block partial of the
+// site block sb.  Every thread of the block must call it (block_sum
+// synchronises the block).
 template <class Op, int EPI, int K, int CP>
 __device__ __forceinline__ void site_epilogue(const OpArgs& oa, const EpiArgs& ea, int k0,
                                               unsigned act, int i, bool valid, int sb,
                                               const typename Op::C o[K][Op::NC],
                                               const double alpha[K], double* red) {
-  using P_C = typename Op::C;
-  using R = typename Op::R;
-  using S = typename Op::S;
-  constexpr int NC = Op::NC;
-  const int Vp = oa.g.Vp;
-  const size_t rstride = (size_t)field_planes<typename Op::Pol>(NC) * Vp;
 #pragma unroll
   for (int kk = 0; kk < K; ++kk) {
     if (!((act >> kk) & 1)) continue;   // uniform over the block
     const int k = k0 + kk;
-    const size_t off = (size_t)k * rstride;
     double acc = 0.0;
-    if (valid) {
-      if constexpr (EPI == EPI_STORE || EPI == EPI_STORE_NORM) {
-        const double n2 = st_site<typename Op::Pol, NC>((S*)ea.out + off, Vp, i, o[kk]);
-        if constexpr (EPI == EPI_STORE_NORM) acc = n2;
-      } else if constexpr (EPI == EPI_CG_UPDATE) {
-        acc = cg_update_site<Op, CP>(ea, Vp, k, off, i, alpha[kk], o[kk]);
-      } else if constexpr (EPI == EPI_RESID) {
-        double2* out = (double2*)ea.out + off;
-        const double2* b = (const double2*)ea.b + off;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-          const size_t e = (size_t)q * Vp + i;
-          double2 bv = b[e];
-          double2 w;
-          w.x = bv.x - (double)o[kk][q].x;
-          w.y = bv.y - (double)o[kk][q].y;
-          out[e] = w;
-          acc += w.x * w.x + w.y * w.y;
-        }
-      } else if constexpr (EPI == EPI_LANCZOS) {
-        double2* out = (double2*)ea.out + off;
-        const double2* v = (const double2*)ea.v + off;
-        const double2* vp = (const double2*)ea.vprev + off;
-        const double bp = ea.beta_prev ? *ea.beta_prev : 0.0;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-          const size_t e = (size_t)q * Vp + i;
-          double2 w;
-          w.x = (double)o[kk][q].x - bp * vp[e].x;
-          w.y = (double)o[kk][q].y - bp * vp[e].y;
-          out[e] = w;
-          acc += v[e].x * w.x + v[e].y * w.y;
-        }
-      }
-    }
+    if (valid) acc = site_finish<Op, EPI, CP>(oa, ea, k, i, o[kk], alpha[kk]);
     if constexpr (EPI != EPI_STORE) {
       const double bs = block_sum(acc, red);
       if (threadIdx.x == 0) ea.part[(size_t)k * ea.nbp + sb] = bs;
@@ -314,7 +319,7 @@ stencil_kernel(const OpArgs oa, const typename Op::S* __restrict__ in, const Epi
       alpha[kk] = 0.0;
       if (!((act >> kk) & 1)) continue;
       const int k = k0 + kk;
-      const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red);
+      const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red, partials_per(oa.g.V));
       const double rho = ea.st[k].rho[ea.par];
       alpha[kk] = (tt > 0.0 && isfinite(tt) && isfinite(rho)) ? rho / tt : 0.0;
       if (sb == 0 && threadIdx.x == 0) {

@@ -14,23 +14,32 @@
 
 namespace lq {
 
+// Another kernel of the operator in place of stencil_kernel (false: none for
+// these arguments); specialised where an operator has one.
+template <class Op, int EPI>
+struct OtherKernel {
+  static bool launch(const OpArgs&, const void*, const EpiArgs&, int, hipStream_t) { return false; }
+};
+
 // Systems per thread (K) for the low-precision CG kernels; 1 elsewhere.
 // The low-precision CG_UPDATE kernels come in two cache policies (ea.stream).
 template <template <class, int, bool> class OpT, class P, int NL, bool DAG, int EPI, int K>
 static void launch_k(const OpArgs& oa, const void* in, const EpiArgs& ea, int nrhs,
                      hipStream_t s) {
   using Op = OpT<P, NL, DAG>;
+  if (OtherKernel<Op, EPI>::launch(oa, in, ea, nrhs, s)) return;
   const int ngroups = (nrhs + K - 1) / K;
   const int grid = ea.nbp * ngroups;
   if (grid == 0) return;
+  const dim3 blk(block_of(oa.g.V));
   if constexpr (EPI == EPI_CG_UPDATE && P::id != 0) {
     if (ea.stream) {
-      hipLaunchKernelGGL((stencil_kernel<Op, EPI, K, kStream>), dim3(grid), dim3(kBlock), 0, s,
+      hipLaunchKernelGGL((stencil_kernel<Op, EPI, K, kStream>), dim3(grid), blk, 0, s,
                          oa, (const typename Op::S*)in, ea, ngroups, nrhs);
       return;
     }
   }
-  hipLaunchKernelGGL((stencil_kernel<Op, EPI, K, 0>), dim3(grid), dim3(kBlock), 0, s, oa,
+  hipLaunchKernelGGL((stencil_kernel<Op, EPI, K, 0>), dim3(grid), blk, 0, s, oa,
                      (const typename Op::S*)in, ea, ngroups, nrhs);
 }
 

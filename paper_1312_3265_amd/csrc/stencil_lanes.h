@@ -185,11 +185,12 @@ struct WilsonLanesOp {
 // The lanes stencil with the epilogues of the batched CG: STORE, STORE_NORM
 // (t = M p, ||t||^2) and CG_UPDATE (q = M^dag t, r -= alpha q, ||r||^2, the
 // grouped x update).  Grid: nbp site blocks x ceil(nrhs / 4) system groups,
-// in the block orders of map_block / map_block_tiled.
+// in the block orders of map_block / map_block_tiled; nb = blocks of 256 sites
+// (a multiple of 8); chunked: the site blocks, and so the partials, are of 64.
 template <class Op, int EPI, int CP>
 __global__ void __launch_bounds__(kLanesBlock)
 stencil_lanes_kernel(const OpArgs oa, const typename Op::S* __restrict__ in, const EpiArgs ea,
-                     int ngroups, int nrhs) {
+                     int nb, int chunked, int ngroups, int nrhs) {
   using C = typename Op::C;
   using S = typename Op::S;
   using Pol = typename Op::Pol;
@@ -199,8 +200,8 @@ stencil_lanes_kernel(const OpArgs oa, const typename Op::S* __restrict__ in, con
   __shared__ double part4[4][4];
   int sb, kg;
   if ((ea.window != -3 && ea.window != -4) ||
-      !map_block_tiled(oa.g, ea.nbp, ngroups, ea.window, sb, kg))
-    map_block(ea.nbp, ngroups, ea.window < -2 ? 0 : ea.window, sb, kg);
+      !map_block_tiled(oa.g, nb, ngroups, ea.window, sb, kg))
+    map_block(nb, ngroups, ea.window < -2 ? 0 : ea.window, sb, kg);
   const int k0 = ea.k0 + kg * 4;
   unsigned act = 0;
 #pragma unroll
@@ -228,7 +229,7 @@ stencil_lanes_kernel(const OpArgs oa, const typename Op::S* __restrict__ in, con
     for (int jj = 0; jj < 4; ++jj) {
       if (!((act >> jj) & 1)) continue;   // uniform over the block
       const int k = k0 + jj;
-      const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red);
+      const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red, chunked ? 4 : 1);
       const double rho = ea.st[k].rho[ea.par];
       const double al = (tt > 0.0 && isfinite(tt) && isfinite(rho)) ? rho / tt : 0.0;
       if (jj == j) alpha = al;
@@ -273,9 +274,15 @@ stencil_lanes_kernel(const OpArgs oa, const typename Op::S* __restrict__ in, con
     if (ln == 0) part4[rj][ch] = v;
     __syncthreads();
     if (t < 4 && ((act >> t) & 1)) {
-      double s = 0.0;
-      for (int c2 = 0; c2 < 4; ++c2) s += part4[t][c2];
-      ea.part[(size_t)(k0 + t) * ea.nbp + sb] = s;
+      double* part = ea.part + (size_t)(k0 + t) * ea.nbp;
+      if (!chunked) {
+        double s = 0.0;
+        for (int c2 = 0; c2 < 4; ++c2) s += part4[t][c2];
+        part[sb] = s;
+      } else {   // one partial per 64 sites
+        for (int c2 = 0; c2 < 4; ++c2)
+          if (4 * sb + c2 < ea.nbp) part[4 * sb + c2] = part4[t][c2];
+      }
     }
   }
 }

@@ -89,7 +89,7 @@ wilson_tsweep_kernel(const OpArgs oa, const double2* __restrict__ in, const EpiA
 
   double alpha[1] = {0.0};
   if constexpr (EPI == EPI_CG_UPDATE) {
-    const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red);
+    const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red, 1);
     const double rho = ea.st[k].rho[ea.par];
     alpha[0] = (tt > 0.0 && isfinite(tt) && isfinite(rho)) ? rho / tt : 0.0;
     if (p == 0 && z == 0 && tc == 0 && tid == 0) {   // the block holding site block 0
@@ -312,7 +312,7 @@ wilson_tsweep_lo_kernel(const OpArgs oa, const typename P::S* __restrict__ in, c
 
   double alpha[1] = {0.0};
   if constexpr (EPI == EPI_CG_UPDATE) {
-    const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red);
+    const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red, 1);
     const double rho = ea.st[k].rho[ea.par];
     alpha[0] = (tt > 0.0 && isfinite(tt) && isfinite(rho)) ? rho / tt : 0.0;
     if (p == 0 && z == 0 && tc == 0 && tid == 0) {   // the block holding site block 0
