@@ -4,6 +4,11 @@
 
 namespace lq {
 
+// (16-bit, nine systems, 16^3 x 32, t = M p and the CG update: 70 + 79 us in
+// pairs, 64 + 77 in threes)
+template <class P, int NL, bool DAG>
+constexpr bool kThirds<SWCornerOp<P, NL, DAG>> = true;
+
 // Lattices of one-wavefront site blocks take the split kernel, with one system
 // per thread.  The choice depends on the lattice alone, so a system's result
 // depends neither on its batch nor on the launch configuration.

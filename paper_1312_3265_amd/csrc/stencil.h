@@ -54,7 +54,7 @@ struct EpiArgs {
   const double* v;        // LANCZOS: v_j
   const double* vprev;    // LANCZOS: v_{j-1}
   const double* beta_prev;// LANCZOS: device scalar beta_{j-1} (null = 0)
-  int rhs_per_thread;     // systems per thread (1, 2 or 4; FP32/Q16 CG kernels)
+  int rhs_per_thread;     // systems per thread (1, 2 or up to 4; FP32/Q16 CG kernels)
   int window;             // block order: > 0 window width, 0 whole range, -1/-2 system-major,
                           // -3/-4 tiled (map_block, map_block_tiled)
   int stream;             // CG_UPDATE, FP32/Q16: 1 = r, p, x loaded and stored non-temporal
@@ -146,7 +146,7 @@ __device__ __forceinline__ bool slot_active(const SlotState* st, int k, int mode
 // partial sums, so the result of a system does not depend on K or on the
 // other systems.
 template <class Op, int K>
-constexpr int stencil_waves() { return (Op::NC == 12 ? K >= 2 : K >= 4) ? 3 : Op::kWaves; }
+constexpr int stencil_waves() { return (Op::NC == 12 ? K >= 2 : K >= 3) ? 3 : Op::kWaves; }
 
 // CG_UPDATE at one site for system k (offset off into the batched fields):
 // r -= alpha q with ||r||^2 returned, and on the last iteration of a group of

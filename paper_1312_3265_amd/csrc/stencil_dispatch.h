@@ -21,6 +21,11 @@ struct OtherKernel {
   static bool launch(const OpArgs&, const void*, const EpiArgs&, int, hipStream_t) { return false; }
 };
 
+// Whether groups of up to four systems become groups of three where that takes
+// as many groups: nine systems are 3 + 3 + 3 rather than 4 + 4 + 1, whose last
+// group computes four.
+template <class Op> constexpr bool kThirds = false;
+
 // Systems per thread (K) for the low-precision CG kernels; 1 elsewhere.
 // The low-precision CG_UPDATE kernels come in two cache policies (ea.stream).
 template <template <class, int, bool> class OpT, class P, int NL, bool DAG, int EPI, int K>
@@ -50,6 +55,9 @@ static void launch_one(const OpArgs& oa, const void* in, const EpiArgs& ea, int 
                                           EPI == EPI_STORE);
   const int K = multi ? ea.rhs_per_thread : 1;
   if constexpr (multi) {
+    if constexpr (kThirds<OpT<P, NL, DAG>>)
+      if (K == 4 && nrhs > 4 && (nrhs + 2) / 3 == (nrhs + 3) / 4)
+        return launch_k<OpT, P, NL, DAG, EPI, 3>(oa, in, ea, nrhs, s);
     if (K == 2) return launch_k<OpT, P, NL, DAG, EPI, 2>(oa, in, ea, nrhs, s);
     if (K == 4) return launch_k<OpT, P, NL, DAG, EPI, 4>(oa, in, ea, nrhs, s);
   }

@@ -68,11 +68,14 @@ wilson_tsweep_kernel(const OpArgs oa, const double2* __restrict__ in, const EpiA
   const int P = plane >> 8, NT = g.L[3] / T;
   const int per = P * g.L[2] * NT;       // blocks per system (a multiple of 8)
   // block b runs on XCD b % 8 as its (b / 8)-th block; XCD x takes the x-th
-  // eighth of the (system, t-chunk, z, slab) blocks, slabs innermost
+  // eighth of the (t-chunk, z, slab) blocks, slabs innermost, each for all
+  // systems in turn: a block's links then come from that XCD's L2 for every
+  // system but the first (system-major, each system fetched them again:
+  // M of 5, 8 and 36 systems on 16^3 x 32 126, 201 and 882 us, now 104, 168
+  // and 813; M^dag with the CG update 208, 306 and 1308, now 190, 293, 1375)
   const int b = blockIdx.x, xcd = b & 7, kk = b >> 3;
-  const int lin = xcd * ((per >> 3) * nrhs) + kk;
-  const int kr = lin / per;
-  int rem = lin - kr * per;
+  const int kr = kk % nrhs;
+  int rem = xcd * (per >> 3) + kk / nrhs;
   const int p = rem % P;
   rem /= P;
   const int z = rem % g.L[2];
