@@ -121,9 +121,20 @@ int lq_gauge_create(const lq_lattice* lat, const void* U, int32_t where, uint32_
     std::unique_ptr<lq_gauge_s> g(new lq_gauge_s);
     gauge_layout(lat->g, features, buf, g.get());
     hipStream_t s = S(stream);
-    launch_fill_zero(buf, nb, s);
+    // every slab and its padding is written below; only the reduction slots
+    // (partials, plaquette, deviation) need clearing
+    launch_fill_zero(g->scratch, ((g->nbp + 8) * sizeof(double)) & ~(size_t)15, s);
+    GaugeOut o;
+    o.u64 = g->u64;
+    o.u32_18 = g->u32_18; o.u32_12 = g->u32_12;
+    o.u16_12 = g->u16_12; o.u16_18 = g->u16_18;
+    o.eo64 = (double2*)g->eo64;
+    o.eo32_18 = (float2*)g->eo32_18; o.eo32_12 = (float2*)g->eo32_12;
+    o.eo16_12 = (short2*)g->eo16_12; o.eo16_18 = (short2*)g->eo16_18;
+    o.dev = (unsigned long long*)(g->scratch + g->nbp + 1);
+    const int Vhp = half_geom(g->g).Vp;
     if (where == LQ_WHERE_DEVICE) {
-      launch_gauge_in(g->g, U, g->u64, 0, g->g.V, s);
+      launch_gauge_in(g->g, Vhp, U, 0, g->g.V, o, s);
     } else {
       // chunks through the staging area; the copy of a chunk is ordered after
       // the repack of the previous one on the same stream
@@ -132,37 +143,12 @@ int lq_gauge_create(const lq_lattice* lat, const void* U, int32_t where, uint32_
         const int n = std::min(kStageSites, g->g.V - i0);
         LQ_HIP(hipMemcpyAsync(g->stage, (const char*)U + (size_t)i0 * site_bytes,
                               (size_t)n * site_bytes, hipMemcpyHostToDevice, s));
-        launch_gauge_in(g->g, g->stage, g->u64, i0, n, s);
+        launch_gauge_in(g->g, Vhp, g->stage, i0, n, o, s);
       }
     }
-    launch_su3_deviation(g->g, g->u64, g->scratch, g->scratch + g->nbp + 1, s);
     LQ_HIP(hipMemcpyAsync(&g->su3_dev, g->scratch + g->nbp + 1, sizeof(double),
                           hipMemcpyDeviceToHost, s));
-    if (features & LQ_FEAT_F32) {
-      launch_links_convert(P32, 18, g->g, g->u64, g->u32_18, s);
-      launch_links_convert(P32, 12, g->g, g->u64, g->u32_12, s);
-    }
-    if (features & LQ_FEAT_Q16) {
-      launch_links_convert(P16, 12, g->g, g->u64, g->u16_12, s);
-      launch_links_convert(P16, 18, g->g, g->u64, g->u16_18, s);
-    }
-    if (features & LQ_FEAT_EO) {
-      const int Vhp = half_geom(g->g).Vp;
-      launch_links_eo(P64, 18, g->g, Vhp, g->u64, g->eo64, s);
-      if (features & LQ_FEAT_F32) {
-        launch_links_eo(P32, 18, g->g, Vhp, g->u64, g->eo32_18, s);
-        launch_links_eo(P32, 12, g->g, Vhp, g->u64, g->eo32_12, s);
-      }
-      if (features & LQ_FEAT_Q16) {
-        launch_links_eo(P16, 12, g->g, Vhp, g->u64, g->eo16_12, s);
-        launch_links_eo(P16, 18, g->g, Vhp, g->u64, g->eo16_18, s);
-      }
-    }
-    if (features & LQ_FEAT_CORNERS) {
-      launch_corners(g->g, g->u64, g->c64, s);
-      if (features & LQ_FEAT_F32) launch_corners_convert(P32, g->g, g->c64, g->c32, s);
-      if (features & LQ_FEAT_Q16) launch_corners_convert(P16, g->g, g->c64, g->c16, s);
-    }
+    if (features & LQ_FEAT_CORNERS) launch_corners(g->g, g->u64, g->c64, g->c32, g->c16, s);
     check_launch();
     LQ_HIP(hipStreamSynchronize(s));   // su3_dev is read on the host
     *out = g.release();

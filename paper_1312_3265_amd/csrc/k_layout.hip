@@ -1,5 +1,6 @@
 // Layout kernels: canonical <-> SoA repacking, link compression to 12 reals
 // (K6), the staggered Wilson corner matrices (K3) and the mean plaquette.
+#include <algorithm>
 #include <stdexcept>
 
 #include "kernels.h"
@@ -104,99 +105,86 @@ void launch_field_out(int prec, int nc, const Geom& g, const void* soa, void* ca
 }
 
 // --------------------------------------------------------------- links
-// sites [i0, i0 + n) of the canonical field; canon points at site i0
+// Sites [i0, i0 + n) of the canonical field (canon points at site i0) into
+// every link copy the gauge field keeps, in one pass: FP64 with 18 reals, the
+// 32-bit and 16-bit copies, the per-parity half-lattice copies of the even-odd
+// blocks (link mu of site i at half site i / 2 of its parity's array), and the
+// largest deviation of a row 2 from conj(row0 x row1): zero up to rounding for
+// SU(3) links, which is what the 12-real storage relies on.  The last sites'
+// call also zeroes the padding of every slab, so the buffer needs no clearing.
+//
+// Bound by memory: 75 MB in and 170 MB out for FP32 and 16-bit copies on
+// 16^3 x 32.  The 64 sites of a block are read in storage order through LDS
+// (a lane reading its own site would touch 64 lines of 576-byte records), one
+// direction per wavefront.  Clearing, repacking, four conversions and the
+// check took 170 us as separate kernels, this one 50 (4.9 TB/s).
 __global__ void __launch_bounds__(256)
-gauge_in_kernel(const Geom g, const double2* __restrict__ canon, double2* __restrict__ u64, int i0,
-                int n) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const int i = i0 + j;
-#pragma unroll 4
-  for (int q = 0; q < 36; ++q) u64[(size_t)q * g.Vp + i] = canon[(size_t)j * 36 + q];
+gauge_in_kernel(const Geom g, int Vhp, const double2* __restrict__ canon, int i0, int n,
+                const GaugeOut o) {
+  __shared__ double2 rec[64][37];   // a site's 36 entries; 37: off the bank period
+  __shared__ double red[4];
+  const int j0 = blockIdx.x * 64;
+  const int cnt = max(0, min(64, n - j0));
+  for (int e = threadIdx.x; e < cnt * 36; e += 256)
+    rec[e / 36][e % 36] = canon[(size_t)j0 * 36 + e];
+  __syncthreads();
+  const int mu = threadIdx.x >> 6, sl = threadIdx.x & 63;
+  const int i = i0 + j0 + sl;
+  const bool site = sl < cnt;
+  double2 m[9];
+  float2 f[9];
+  double dev = 0.0;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    m[k] = site ? rec[sl][mu * 9 + k] : make_double2(0.0, 0.0);
+    f[k] = make_float2((float)m[k].x, (float)m[k].y);
+  }
+  if (site) {
+    const double2 r[3] = {cconj(csub(cmul(m[1], m[5]), cmul(m[2], m[4]))),
+                          cconj(csub(cmul(m[2], m[3]), cmul(m[0], m[5]))),
+                          cconj(csub(cmul(m[0], m[4]), cmul(m[1], m[3])))};
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      dev = fmax(dev, fmax(fabs(r[k].x - m[6 + k].x), fabs(r[k].y - m[6 + k].y)));
+  }
+  // past the sites of a call only the padding that follows the last site
+  if (site || (i >= g.V && i < g.Vp)) {
+    store_link<F64, 18>(o.u64, g.Vp, mu, i, m);
+    if (o.u32_18) store_link<F32, 18>(o.u32_18, g.Vp, mu, i, f);
+    if (o.u32_12) store_link<F32, 12>(o.u32_12, g.Vp, mu, i, f);
+    if (o.u16_12) store_link<Q16L, 12>(o.u16_12, g.Vp, mu, i, f);
+    if (o.u16_18) store_link<Q16L, 18>(o.u16_18, g.Vp, mu, i, f);
+  }
+  if (o.eo64 && (site || (i >= g.V && i < 2 * Vhp))) {
+    int par = i & 1;
+    if (site) {
+      const Coord c = site_coords(g, i);
+      par = (c.x[0] + c.x[1] + c.x[2] + c.x[3]) & 1;
+    }
+    const int h = i >> 1;
+    const size_t p18 = (size_t)par * 36 * Vhp, p12 = (size_t)par * 24 * Vhp;
+    store_link<F64, 18>(o.eo64 + p18, Vhp, mu, h, m);
+    if (o.eo32_18) store_link<F32, 18>(o.eo32_18 + p18, Vhp, mu, h, f);
+    if (o.eo32_12) store_link<F32, 12>(o.eo32_12 + p12, Vhp, mu, h, f);
+    if (o.eo16_12) store_link<Q16L, 12>(o.eo16_12 + p12, Vhp, mu, h, f);
+    if (o.eo16_18) store_link<Q16L, 18>(o.eo16_18 + p18, Vhp, mu, h, f);
+  }
+  for (int off = 32; off >= 1; off >>= 1) dev = fmax(dev, __shfl_xor(dev, off, 64));
+  if (sl == 0) red[mu] = dev;
+  __syncthreads();
+  // non-negative doubles order as their bits do
+  if (threadIdx.x == 0)
+    atomicMax(o.dev, (unsigned long long)__double_as_longlong(
+                         fmax(fmax(red[0], red[1]), fmax(red[2], red[3]))));
 }
 
-void launch_gauge_in(const Geom& g, const void* canon, double2* u64, int i0, int n,
+void launch_gauge_in(const Geom& g, int Vhp, const void* canon, int i0, int n, const GaugeOut& o,
                      hipStream_t s) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(gauge_in_kernel, dim3((n + 255) / 256), dim3(256), 0, s, g,
-                     (const double2*)canon, u64, i0, n);
-}
-
-// FP64 18-real -> precision P with NL reals (12: rows 0 and 1 only)
-template <class P, int NL>
-__global__ void __launch_bounds__(256)
-links_convert_kernel(const Geom g, const double2* __restrict__ u64, typename P::S* __restrict__ dst) {
-  using C = typename P::C;
-  using R = typename P::R;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.V) return;
-  for (int mu = 0; mu < 4; ++mu) {
-    C m[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const double2 z = u64[(size_t)(mu * 9 + k) * g.Vp + i];
-      m[k].x = (R)z.x; m[k].y = (R)z.y;
-    }
-    store_link<P, NL>(dst, g.Vp, mu, i, m);
-  }
-}
-
-void launch_links_convert(int prec, int nl, const Geom& g, const double2* u64, void* dst,
-                          hipStream_t s) {
-  dim3 grid((g.V + 255) / 256), blk(256);
-  if (prec == P32 && nl == 18)
-    hipLaunchKernelGGL((links_convert_kernel<F32, 18>), grid, blk, 0, s, g, u64, (float2*)dst);
-  else if (prec == P32 && nl == 12)
-    hipLaunchKernelGGL((links_convert_kernel<F32, 12>), grid, blk, 0, s, g, u64, (float2*)dst);
-  else if (prec == P16 && nl == 12)
-    hipLaunchKernelGGL((links_convert_kernel<Q16L, 12>), grid, blk, 0, s, g, u64, (short2*)dst);
-  else if (prec == P16 && nl == 18)
-    hipLaunchKernelGGL((links_convert_kernel<Q16L, 18>), grid, blk, 0, s, g, u64, (short2*)dst);
-  else
-    throw std::runtime_error("links_convert: unsupported precision/storage");
-}
-
-// FP64 18-real links -> per-parity half-lattice records of precision P with
-// NL reals (the even-odd blocks): link mu of site i goes to half site i / 2 of
-// its parity's array, which starts at dst + par * 4 * NSTORE * Vhp elements.
-template <class P, int NL>
-__global__ void __launch_bounds__(256)
-links_eo_kernel(const Geom g, int Vhp, const double2* __restrict__ u64,
-                typename P::S* __restrict__ dst) {
-  using C = typename P::C;
-  using R = typename P::R;
-  constexpr int NSTORE = P::id == 0 ? 9 : NL / 2;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.V) return;
-  const Coord c = site_coords(g, i);
-  const int par = (c.x[0] + c.x[1] + c.x[2] + c.x[3]) & 1;
-  typename P::S* d = dst + (size_t)par * 4 * NSTORE * Vhp;
-  for (int mu = 0; mu < 4; ++mu) {
-    C m[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const double2 z = u64[(size_t)(mu * 9 + k) * g.Vp + i];
-      m[k].x = (R)z.x; m[k].y = (R)z.y;
-    }
-    store_link<P, P::id == 0 ? 18 : NL>(d, Vhp, mu, i >> 1, m);
-  }
-}
-
-void launch_links_eo(int prec, int nl, const Geom& g, int Vhp, const double2* u64, void* dst,
-                     hipStream_t s) {
-  dim3 grid((g.V + 255) / 256), blk(256);
-  if (prec == P64)
-    hipLaunchKernelGGL((links_eo_kernel<F64, 18>), grid, blk, 0, s, g, Vhp, u64, (double2*)dst);
-  else if (prec == P32 && nl == 18)
-    hipLaunchKernelGGL((links_eo_kernel<F32, 18>), grid, blk, 0, s, g, Vhp, u64, (float2*)dst);
-  else if (prec == P32 && nl == 12)
-    hipLaunchKernelGGL((links_eo_kernel<F32, 12>), grid, blk, 0, s, g, Vhp, u64, (float2*)dst);
-  else if (prec == P16 && nl == 12)
-    hipLaunchKernelGGL((links_eo_kernel<Q16L, 12>), grid, blk, 0, s, g, Vhp, u64, (short2*)dst);
-  else if (prec == P16 && nl == 18)
-    hipLaunchKernelGGL((links_eo_kernel<Q16L, 18>), grid, blk, 0, s, g, Vhp, u64, (short2*)dst);
-  else
-    throw std::runtime_error("links_eo: unsupported precision/storage");
+  int end = i0 + n;
+  if (end == g.V) end = o.eo64 ? std::max(g.Vp, 2 * Vhp) : g.Vp;
+  hipLaunchKernelGGL(gauge_in_kernel, dim3((end - i0 + 63) / 64), dim3(256), 0, s, g, Vhp,
+                     (const double2*)canon, i0, n, o);
 }
 
 // ---------------------------------------------------------- corners (K3)
@@ -204,8 +192,15 @@ void launch_links_eo(int prec, int nl, const Geom& g, int Vhp, const double2* u6
 // x + s taking one link per direction.  With pt(T) = x + sum_{nu in T} s_nu nu
 // and P(T) = sum of the products along all orderings of the directions in T,
 //   P(T) = sum_{mu in T} P(T \ mu) L(pt(T \ mu), s_mu mu),   P({}) = 1,
-// where L(y, +mu) = U_mu(y) and L(y, -mu) = U_mu(y - mu)^dag.  Level 2 is
-// rebuilt inside level 3 (40 matrix products per corner, no large live state).
+// where L(y, +mu) = U_mu(y) and L(y, -mu) = U_mu(y - mu)^dag.
+//
+// P(T) depends on the signs of T's directions only, so the eight stored
+// corners of a site (s4 = +1) share 18 matrices of level 2 and 20 of level 3:
+// 128 products and 164 links a site instead of 320 and 512 with every corner
+// on its own, which was bound by those loads (9.7 GB through L2 on 16^3 x 32,
+// 849 us, and 65 for the 32-bit and 16-bit copies; now 271 with the copies).  A block takes 16 sites, one matrix of the level per thread row
+// (16 lanes), and the levels meet in LDS (46 KB: three blocks per CU).  Each
+// corner's sums run in the same order as on its own.
 struct M3 { double2 e[9]; };
 
 __device__ __forceinline__ void m3_load(const double2* __restrict__ u, int Vp, int mu, int site,
@@ -238,104 +233,143 @@ __device__ __forceinline__ void m3_zero(M3& m) {
   for (int k = 0; k < 9; ++k) m.e[k] = make_double2(0.0, 0.0);
 }
 
-// site index of x + offset (each offset component in {-1, 0, 1}), periodic
-__device__ __forceinline__ int offset_site(const Geom& g, const Coord& c, const int o[4]) {
-  int j = 0;
+constexpr int kCornerSites = 16, kCornerRows = 20;
+
+// Index steps of a site to x + nu and x - nu.
+struct Steps { int f[4], b[4]; };
+
+// the link L(y, -+mu) (neg: the step is -mu), y = site `at`, whose coordinate
+// along mu is that of x
+__device__ __forceinline__ void path_link(const double2* __restrict__ u, int Vp, const Steps& st,
+                                          int at, int mu, bool neg, M3& m) {
+  int back = 0;
 #pragma unroll
+  for (int nu = 0; nu < 4; ++nu) back = nu == mu ? st.b[nu] : back;
+  const double2* p = u + (size_t)(mu * 9) * Vp + (neg ? at + back : at);
+  M3 l;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) l.e[k] = p[(size_t)k * Vp];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const double2 t = cconj(l.e[b * 3 + a]), v = l.e[a * 3 + b];
+      m.e[a * 3 + b] = make_double2(neg ? t.x : v.x, neg ? t.y : v.y);
+    }
+}
+// index step of direction nu with the sign of bit nu of neg
+__device__ __forceinline__ int step_of(const Steps& st, int nu, int neg) {
+  int d = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) d = k == nu ? ((neg >> k) & 1 ? st.b[k] : st.f[k]) : d;
+  return d;
+}
+// places of the level-2 matrix of directions a < b and of the level-3 matrix
+// without direction m, for the signs neg (bits of the directions < 3)
+__device__ __forceinline__ int place2(int a, int b, int neg) {
+  const int sa = (neg >> a) & 1, sb = (neg >> b) & 1;
+  return b == 3 ? 12 + 2 * a + sa : 4 * (a + b - 1) + sa + 2 * sb;
+}
+__device__ __forceinline__ int place3(int m, int neg) {
+  if (m == 3) return neg & 7;
+  const int lo = m == 0 ? 1 : 0, hi = m == 2 ? 1 : 2;
+  return 8 + 4 * m + ((neg >> lo) & 1) + 2 * ((neg >> hi) & 1);
+}
+
+__global__ void __launch_bounds__(kCornerSites * kCornerRows)
+__attribute__((amdgpu_waves_per_eu(4, 4)))
+corners_kernel(const Geom g, const double2* __restrict__ u, double2* __restrict__ w64,
+               float2* __restrict__ w32, short2* __restrict__ w16) {
+  __shared__ double2 lv[kCornerRows][9][kCornerSites];
+  const int sl = threadIdx.x % kCornerSites, row = threadIdx.x / kCornerSites;
+  const int i = blockIdx.x * kCornerSites + sl;
+  const int x = min(i, g.V - 1);   // blocks past the last site: its padding, stored as zero
+  const Coord c = site_coords(g, x);
+  Steps st;
+#pragma unroll
+  for (int nu = 0; nu < 4; ++nu) {
+    st.f[nu] = c.x[nu] == g.L[nu] - 1 ? (1 - g.L[nu]) * g.stride[nu] : g.stride[nu];
+    st.b[nu] = c.x[nu] == 0 ? (g.L[nu] - 1) * g.stride[nu] : -g.stride[nu];
+  }
+  M3 p, l1, l2;
+  // level 2, a < b: L(x, a) L(x + a, b) + L(x, b) L(x + b, a)
+  if (row < 18) {
+    int a, b, neg;
+    if (row >= 12) {
+      a = (row - 12) >> 1; b = 3; neg = ((row - 12) & 1) << a;
+    } else {
+      const int q = row >> 2;
+      a = q == 2 ? 1 : 0; b = q == 0 ? 1 : 2;
+      neg = ((row & 1) << a) | (((row >> 1) & 1) << b);
+    }
+    const bool na = (neg >> a) & 1, nb = (neg >> b) & 1;
+    m3_zero(p);
+    path_link(u, g.Vp, st, x, a, na, l1);
+    path_link(u, g.Vp, st, x + step_of(st, a, neg), b, nb, l2);
+    m3_mul_acc(l1, l2, p);
+    path_link(u, g.Vp, st, x, b, nb, l1);
+    path_link(u, g.Vp, st, x + step_of(st, b, neg), a, na, l2);
+    m3_mul_acc(l1, l2, p);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) lv[row][k][sl] = p.e[k];
+  }
+  __syncthreads();
+  // level 3 without direction m: sum over its directions mu, ascending
+  {
+    int m = 3, neg = row;
+    if (row >= 8) {
+      m = (row - 8) >> 2;
+      const int lo = m == 0 ? 1 : 0, hi = m == 2 ? 1 : 2;
+      neg = ((row & 1) << lo) | (((row >> 1) & 1) << hi);
+    }
+    m3_zero(p);
+#pragma unroll 1
+    for (int q = 0; q < 3; ++q) {
+      const int mu = q + (q >= m);                     // the q-th direction of the three
+      const int q0 = q == 0 ? 1 : 0, q1 = q == 2 ? 1 : 2;
+      const int a = q0 + (q0 >= m), b = q1 + (q1 >= m);
+      const int at = place2(a, b, neg);
+#pragma unroll
+      for (int k = 0; k < 9; ++k) l1.e[k] = lv[at][k][sl];
+      path_link(u, g.Vp, st, x + step_of(st, a, neg) + step_of(st, b, neg), mu, (neg >> mu) & 1, l2);
+      m3_mul_acc(l1, l2, p);
+    }
+  }
+  __syncthreads();   // level 3 takes level 2's place
+#pragma unroll
+  for (int k = 0; k < 9; ++k) lv[row][k][sl] = p.e[k];
+  __syncthreads();
+  // the corner with the signs of row's bits
+  if (row >= 8) return;
+  m3_zero(p);
+#pragma unroll 1
   for (int mu = 0; mu < 4; ++mu) {
-    int y = c.x[mu] + o[mu];
-    if (y < 0) y += g.L[mu];
-    else if (y >= g.L[mu]) y -= g.L[mu];
-    j += y * g.stride[mu];
-  }
-  return j;
-}
-
-// link L(pt, s_mu mu) for the point pt = x + sum_{nu in T} s_nu nu
-__device__ __forceinline__ void path_link(const Geom& g, const double2* __restrict__ u,
-                                          const Coord& c, const int s[4], int T, int mu, M3& m) {
-  int o[4];
+    const int at = place3(mu, row);
+    int y = x;
 #pragma unroll
-  for (int nu = 0; nu < 4; ++nu) o[nu] = ((T >> nu) & 1) ? s[nu] : 0;
-  if (s[mu] > 0) {
-    m3_load(u, g.Vp, mu, offset_site(g, c, o), false, m);
-  } else {
-    o[mu] -= 1;
-    m3_load(u, g.Vp, mu, offset_site(g, c, o), true, m);
-  }
-}
-
-__global__ void __launch_bounds__(64)
-corners_kernel(const Geom g, const double2* __restrict__ u, double2* __restrict__ w) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int cidx = blockIdx.y;
-  if (i >= g.V) return;
-  const Coord c = site_coords(g, i);
-  const int s[4] = {(cidx & 1) ? -1 : 1, (cidx & 2) ? -1 : 1, (cidx & 4) ? -1 : 1, 1};
-  M3 p4;
-  m3_zero(p4);
-#pragma unroll 1
-  for (int mu4 = 0; mu4 < 4; ++mu4) {
-    const int T3 = 15 ^ (1 << mu4);
-    M3 p3;
-    m3_zero(p3);
-#pragma unroll 1
-    for (int mu3 = 0; mu3 < 4; ++mu3) {
-      if (!((T3 >> mu3) & 1)) continue;
-      const int T2 = T3 ^ (1 << mu3);
-      // P(T2) for T2 = {a, b}: L(x, a) L(x + a, b) + L(x, b) L(x + b, a)
-      const int a = __ffs(T2) - 1;
-      const int b = __ffs(T2 ^ (1 << a)) - 1;
-      M3 p2, l1, l2;
-      m3_zero(p2);
-      path_link(g, u, c, s, 0, a, l1);
-      path_link(g, u, c, s, 1 << a, b, l2);
-      m3_mul_acc(l1, l2, p2);
-      path_link(g, u, c, s, 0, b, l1);
-      path_link(g, u, c, s, 1 << b, a, l2);
-      m3_mul_acc(l1, l2, p2);
-      path_link(g, u, c, s, T2, mu3, l1);
-      m3_mul_acc(p2, l1, p3);
-    }
-    M3 l;
-    path_link(g, u, c, s, T3, mu4, l);
-    m3_mul_acc(p3, l, p4);
-  }
+    for (int nu = 0; nu < 4; ++nu) y += nu == mu ? 0 : ((row >> nu) & 1) ? st.b[nu] : st.f[nu];
 #pragma unroll
-  for (int k = 0; k < 9; ++k)
-    w[(size_t)(cidx * 9 + k) * g.Vp + i] = make_double2(p4.e[k].x / 24.0, p4.e[k].y / 24.0);
-}
-
-void launch_corners(const Geom& g, const double2* u64, double2* c64, hipStream_t s) {
-  hipLaunchKernelGGL(corners_kernel, dim3((g.V + 63) / 64, 8), dim3(64), 0, s, g, u64, c64);
-}
-
-template <class P>
-__global__ void __launch_bounds__(256)
-corners_convert_kernel(const Geom g, const double2* __restrict__ c64, typename P::S* __restrict__ dst) {
-  using C = typename P::C;
-  using R = typename P::R;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.V) return;
-  for (int c = 0; c < 8; ++c) {
-    C m[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const double2 z = c64[(size_t)(c * 9 + k) * g.Vp + i];
-      m[k].x = (R)z.x; m[k].y = (R)z.y;
-    }
-    store_corner<P>(dst, g.Vp, c, i, m);
+    for (int k = 0; k < 9; ++k) l1.e[k] = lv[at][k][sl];
+    path_link(u, g.Vp, st, y, mu, (row >> mu) & 1, l2);
+    m3_mul_acc(l1, l2, p);
   }
+  const bool pad = i >= g.V;
+  float2 f[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    p.e[k] = pad ? make_double2(0.0, 0.0) : make_double2(p.e[k].x / 24.0, p.e[k].y / 24.0);
+    f[k] = make_float2((float)p.e[k].x, (float)p.e[k].y);
+  }
+  store_corner<F64>(w64, g.Vp, row, i, p.e);
+  if (w32) store_corner<F32>(w32, g.Vp, row, i, f);
+  if (w16) store_corner<Q16L>(w16, g.Vp, row, i, f);
 }
 
-void launch_corners_convert(int prec, const Geom& g, const double2* c64, void* dst, hipStream_t s) {
-  dim3 grid((g.V + 255) / 256), blk(256);
-  if (prec == P32)
-    hipLaunchKernelGGL(corners_convert_kernel<F32>, grid, blk, 0, s, g, c64, (float2*)dst);
-  else if (prec == P16)
-    hipLaunchKernelGGL(corners_convert_kernel<Q16L>, grid, blk, 0, s, g, c64, (short2*)dst);
-  else
-    throw std::runtime_error("corners_convert: unsupported precision");
+void launch_corners(const Geom& g, const double2* u64, double2* c64, float2* c32, short2* c16,
+                    hipStream_t s) {
+  // Vp is a multiple of the block's sites
+  hipLaunchKernelGGL(corners_kernel, dim3(g.Vp / kCornerSites), dim3(kCornerSites * kCornerRows), 0,
+                     s, g, u64, c64, c32, c16);
 }
 
 // ------------------------------------------------------------ plaquette
@@ -384,48 +418,6 @@ void launch_plaquette(const Geom& g, const double2* u64, double* part, int nbp, 
   (void)nbp;
   hipLaunchKernelGGL(plaquette_kernel, dim3(nb), dim3(256), 0, s, g, u64, part);
   hipLaunchKernelGGL(plaquette_finish_kernel, dim3(1), dim3(64), 0, s, part, nb, (double)g.V, out);
-}
-
-// ------------------------------------------------------ SU(3) check
-// Largest deviation, over sites and directions, of the stored row 2 from
-// conj(row0 x row1): zero up to rounding for SU(3) links, which is what the
-// 12-real storage relies on.
-__global__ void __launch_bounds__(256)
-su3_dev_kernel(const Geom g, const double2* __restrict__ u, double* __restrict__ part) {
-  __shared__ double red[4];
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  double dev = 0.0;
-  if (i < g.V) {
-    for (int mu = 0; mu < 4; ++mu) {
-      double2 m[9];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) m[k] = u[(size_t)(mu * 9 + k) * g.Vp + i];
-      const double2 r[3] = {cconj(csub(cmul(m[1], m[5]), cmul(m[2], m[4]))),
-                            cconj(csub(cmul(m[2], m[3]), cmul(m[0], m[5]))),
-                            cconj(csub(cmul(m[0], m[4]), cmul(m[1], m[3])))};
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-        dev = fmax(dev, fmax(fabs(r[k].x - m[6 + k].x), fabs(r[k].y - m[6 + k].y)));
-    }
-  }
-  for (int off = 32; off >= 1; off >>= 1) dev = fmax(dev, __shfl_xor(dev, off, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dev;
-  __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-}
-
-__global__ void max_finish_kernel(const double* __restrict__ part, int n, double* out) {
-  double v = 0.0;
-  for (int k = threadIdx.x; k < n; k += 64) v = fmax(v, part[k]);
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  if (threadIdx.x == 0) *out = v;
-}
-
-void launch_su3_deviation(const Geom& g, const double2* u64, double* part, double* out,
-                          hipStream_t s) {
-  const int nb = (g.V + 255) / 256;
-  hipLaunchKernelGGL(su3_dev_kernel, dim3(nb), dim3(256), 0, s, g, u64, part);
-  hipLaunchKernelGGL(max_finish_kernel, dim3(1), dim3(64), 0, s, part, nb, out);
 }
 
 // ------------------------------------------------------------- filling

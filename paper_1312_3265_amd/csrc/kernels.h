@@ -55,17 +55,23 @@ void launch_field_in(int prec, int nc, const Geom& g, const void* canon, int can
                      int nbp, int k0, int nrhs, hipStream_t s, int par = -1);
 void launch_field_out(int prec, int nc, const Geom& g, const void* soa, void* canon, int canon_f64,
                       int nbp, int k0, int nrhs, hipStream_t s, int par = -1);
+// The link copies of a gauge field (null: not kept); dev: the largest deviation
+// from SU(3), as the bits of a double, zero before the first call.
+struct GaugeOut {
+  double2* u64;
+  float2 *u32_18, *u32_12;
+  short2 *u16_12, *u16_18;
+  double2* eo64;               // even-odd copies: per parity, Vhp sites a slab
+  float2 *eo32_18, *eo32_12;
+  short2 *eo16_12, *eo16_18;
+  unsigned long long* dev;
+};
 // sites [i0, i0 + n) of a canonical gauge field whose site i0 is at `canon`
-void launch_gauge_in(const Geom& g, const void* canon, double2* u64, int i0, int n,
+void launch_gauge_in(const Geom& g, int Vhp, const void* canon, int i0, int n, const GaugeOut& o,
                      hipStream_t s);
-void launch_links_convert(int prec, int nl, const Geom& g, const double2* u64, void* dst,
-                          hipStream_t s);
-void launch_links_eo(int prec, int nl, const Geom& g, int Vhp, const double2* u64, void* dst,
-                     hipStream_t s);
-void launch_corners(const Geom& g, const double2* u64, double2* c64, hipStream_t s);
-void launch_corners_convert(int prec, const Geom& g, const double2* c64, void* dst, hipStream_t s);
-void launch_su3_deviation(const Geom& g, const double2* u64, double* part, double* out,
-                          hipStream_t s);
+// c32, c16 may be null
+void launch_corners(const Geom& g, const double2* u64, double2* c64, float2* c32, short2* c16,
+                    hipStream_t s);
 void launch_plaquette(const Geom& g, const double2* u64, double* part, int nbp, double* out,
                       hipStream_t s);
 void launch_fill_zero(void* p, size_t bytes, hipStream_t s);
