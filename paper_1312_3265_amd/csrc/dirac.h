@@ -64,6 +64,8 @@ __device__ __forceinline__ void bdmul(int mu, const C h0, const C h1, C& o0, C& 
   }
 }
 
+template <class P, int NL, bool DAG, int K, bool EO> struct WilsonHops;
+
 template <class P, int NL, bool DAG, bool GENERAL_R = false>
 struct WilsonOp {
   using Pol = P;
@@ -105,11 +107,6 @@ struct WilsonOp {
       }
     }
   }
-
-  template <int K>
-  static constexpr bool kHopPairs() { return P::id != 0 && K == 1; }
-  template <int K>
-  static constexpr bool kStraight() { return P::id != 0 && K >= 2; }
 
   // r = 1 hop along +-MU with the gamma structure fixed at compile time:
   // h = sgn * scale * (psi_up + TT B psi_lo) (TT = -s forward, +s backward),
@@ -261,15 +258,14 @@ struct WilsonOp {
     }
     if constexpr (!GENERAL_R) {
       // Each hop's code has its gamma structure and coordinates built in.
-      // Several FP32/16-bit systems per thread: the eight hops in a straight
-      // line, a scheduling barrier between them so that no hop's loads are
-      // hoisted into an earlier one (a rolled loop would shuffle the K
-      // accumulators through its back edge, a register move per value per
-      // hop).  Otherwise the loop stays rolled (its index made opaque to the
-      // compiler, which would unroll it and hoist every hop's loads into
-      // spills); an iteration covers one hop, or both hops of a direction
-      // where the registers allow (single-system FP32/Q16).
-      if constexpr (kStraight<K>()) {
+      // FP32 and 16-bit: the eight hops in a straight line (a rolled loop would
+      // shuffle the K accumulators through its back edge, a register move per
+      // value per hop): WilsonHops, or, for four systems, hops with scheduling
+      // barriers between them, one system's words at a time (four systems'
+      // words spill).  FP64: the loop stays rolled (its index made opaque to
+      // the compiler, which would unroll it and hoist every hop's loads into
+      // spills).
+      if constexpr (P::id != 0 && K >= 4) {
         hop_r1<0, false, K>(a, in0, rstride, c, i, act, acc);
         __builtin_amdgcn_sched_barrier(0);
         hop_r1<0, true, K>(a, in0, rstride, c, i, act, acc);
@@ -285,22 +281,11 @@ struct WilsonOp {
         hop_r1<3, false, K>(a, in0, rstride, c, i, act, acc);
         __builtin_amdgcn_sched_barrier(0);
         hop_r1<3, true, K>(a, in0, rstride, c, i, act, acc);
-      } else if constexpr (kHopPairs<K>()) {
-#pragma unroll 1
-        for (int m0 = 0; m0 < 4; ++m0) {
-          int mu = m0;
-          asm volatile("" : "+s"(mu));
-          switch (mu) {
-            case 0: hop_r1<0, false, K>(a, in0, rstride, c, i, act, acc);
-                    hop_r1<0, true, K>(a, in0, rstride, c, i, act, acc); break;
-            case 1: hop_r1<1, false, K>(a, in0, rstride, c, i, act, acc);
-                    hop_r1<1, true, K>(a, in0, rstride, c, i, act, acc); break;
-            case 2: hop_r1<2, false, K>(a, in0, rstride, c, i, act, acc);
-                    hop_r1<2, true, K>(a, in0, rstride, c, i, act, acc); break;
-            default: hop_r1<3, false, K>(a, in0, rstride, c, i, act, acc);
-                     hop_r1<3, true, K>(a, in0, rstride, c, i, act, acc); break;
-          }
-        }
+      } else if constexpr (P::id != 0) {
+        using Hops = WilsonHops<P, NL, DAG, K, false>;
+        typename Hops::Words w[Hops::AHEAD + 1];
+        R one[K];
+        Hops::run(g, a.links, a.links, in0, rstride, c, i, i, act, one, w, acc);
       } else {
 #pragma unroll 1
         for (int h0 = 0; h0 < 8; ++h0) {
@@ -343,6 +328,89 @@ struct WilsonOp {
   }
 };
 
+// The eight r = 1 hops of a site for K systems (one or two) in a straight line
+// (FP32 and 16-bit).  A hop's storage words are loaded together; with 16-bit
+// storage and one system per thread, before the arithmetic of the hop before
+// it (a hop's words are 19 registers; the 30 or more of the others' would
+// cost a wave or spill: FP32 with one hop ahead 627 us instead of 544).
+// Waiting for each hop's loads in turn, the 16-bit kernels left an eighth of
+// their time idle: eight systems on 24^3 x 48, M p and the CG update, even-odd
+// 293 + 379 us in the rolled loop, 281 + 353 with one and 260 + 359 with two
+// systems per thread; without even-odd 273 + 510, 264 + 441 and 253 + 492.
+// Wilson: in and links over the lattice, lf = lb.  Even-odd (EO):
+// half-lattice arrays, the neighbour and the link of a backward hop (lb) of
+// the other parity; fm[k] multiplies the hop factors.
+template <class P, int NL, bool DAG, int K, bool EO>
+struct WilsonHops {
+  using W = WilsonOp<P, NL, DAG, false>;
+  using LP = typename LinkPol<P, NL>::type;
+  using C = typename P::C;
+  using R = typename P::R;
+  using S = typename P::S;
+  static constexpr int VW = vec_rec_bytes<P>(12) / 4;
+  static constexpr int AHEAD = P::kSiteScale && K == 1 ? 1 : 0;
+  struct Words {
+    uint32_t m[kLinkWords<LP, NL>];
+    uint32_t v[K][VW];
+  };
+
+  template <int H>
+  __device__ __forceinline__ static int neighbour(const Geom& g, const Coord& c, int i, bool& flip) {
+    constexpr int MU = H >> 1;
+    bool wrap;
+    const int j = (H & 1) ? nb_bwd(g, c, i, MU, wrap) : nb_fwd(g, c, i, MU, wrap);
+    flip = wrap && g.bc[MU] < 0;
+    return EO ? j >> 1 : j;
+  }
+
+  // i: lexicographic site; own: its index in the arrays
+  template <int H = -AHEAD>
+  __device__ __forceinline__ static void run(const Geom& g, const void* lf, const void* lb,
+                                             const S* __restrict__ in0, size_t rstride,
+                                             const Coord& c, int i, int own, unsigned act,
+                                             const R fm[K], Words* w, C acc[K][12]) {
+    if constexpr (H < 8) {
+      constexpr int L = H + AHEAD;
+      if constexpr (L < 8) {
+        Words& n = w[L % (AHEAD + 1)];
+        bool flip;
+        const int j = neighbour<L>(g, c, i, flip);
+        ld_link_words<LP, NL>((const typename LP::S*)((L & 1) ? lb : lf), g.Vp, L >> 1,
+                              (L & 1) ? j : own, n.m);
+        // of the systems that are not selected (or do not exist), another
+        // one's words: no branch, and the result is not used
+        const int k1 = K > 1 ? __ffs(act) - 1 : 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+          ld_rec<4 * VW>(in0 + (K == 1 || ((act >> k) & 1) ? k : k1) * rstride, g.Vp, j, n.v[k]);
+      }
+      if constexpr (H >= 0) {
+        constexpr int MU = H >> 1, s = DAG ? -1 : 1, TT = (H & 1) ? s : -s;
+        __builtin_amdgcn_sched_barrier(0);
+        bool flip;
+        (void)neighbour<H>(g, c, i, flip);
+        const Words& n = w[H % (AHEAD + 1)];
+        C lk[9];
+        dec_link<LP, NL, true>(n.m, lk);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          R sc = (R)1;
+          C h[2][3];
+          W::template project_words<MU, TT>(n.v[k], h, sc);
+          R f = W::template hop_factor<LP>(sc, flip);
+          if constexpr (EO) f *= fm[k];
+          W::template accumulate<MU, TT, (H & 1) != 0>(lk, h, f, acc[k]);
+          // the sums are pinned between the loads before and after them
+#pragma unroll
+          for (int q = 0; q < 12; ++q)
+            asm volatile("" : "+v"(acc[k][q].x), "+v"(acc[k][q].y)::"memory");
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      run<H + 1>(g, lf, lb, in0, rstride, c, i, own, act, fm, w, acc);
+    }
+  }
+};
 // ------------------------------------------------ Wilson, even-odd blocks
 // Half-lattice Wilson blocks for the even-odd preconditioned solve (the
 // preconditioning of the footnote to eq. (2), Sec. 3; r = 1).  A field holds
@@ -438,7 +506,7 @@ struct WilsonEOOp {
 #pragma unroll
       for (int q = 0; q < 12; ++q) acc[k][q] = diag ? cscale(v[q], coef) : czero<C>();
     }
-    if constexpr (W::template kStraight<K>()) {
+    if constexpr (P::id != 0 && K >= 4) {
       hop_eo<0, false, K>(a, in0, rstride, c, i, h, act, fm, acc);
       __builtin_amdgcn_sched_barrier(0);
       hop_eo<0, true, K>(a, in0, rstride, c, i, h, act, fm, acc);
@@ -454,22 +522,10 @@ struct WilsonEOOp {
       hop_eo<3, false, K>(a, in0, rstride, c, i, h, act, fm, acc);
       __builtin_amdgcn_sched_barrier(0);
       hop_eo<3, true, K>(a, in0, rstride, c, i, h, act, fm, acc);
-    } else if constexpr (W::template kHopPairs<K>()) {
-#pragma unroll 1
-      for (int m0 = 0; m0 < 4; ++m0) {
-        int mu = m0;
-        asm volatile("" : "+s"(mu));
-        switch (mu) {
-          case 0: hop_eo<0, false, K>(a, in0, rstride, c, i, h, act, fm, acc);
-                  hop_eo<0, true, K>(a, in0, rstride, c, i, h, act, fm, acc); break;
-          case 1: hop_eo<1, false, K>(a, in0, rstride, c, i, h, act, fm, acc);
-                  hop_eo<1, true, K>(a, in0, rstride, c, i, h, act, fm, acc); break;
-          case 2: hop_eo<2, false, K>(a, in0, rstride, c, i, h, act, fm, acc);
-                  hop_eo<2, true, K>(a, in0, rstride, c, i, h, act, fm, acc); break;
-          default: hop_eo<3, false, K>(a, in0, rstride, c, i, h, act, fm, acc);
-                   hop_eo<3, true, K>(a, in0, rstride, c, i, h, act, fm, acc); break;
-        }
-      }
+    } else if constexpr (P::id != 0) {
+      using Hops = WilsonHops<P, NL, DAG, K, true>;
+      typename Hops::Words w[Hops::AHEAD + 1];
+      Hops::run(g, a.links, a.links_nb, in0, rstride, c, i, h, act, fm, w, acc);
     } else {
 #pragma unroll 1
       for (int h0 = 0; h0 < 8; ++h0) {

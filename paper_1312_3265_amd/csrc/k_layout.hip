@@ -198,9 +198,10 @@ void launch_gauge_in(const Geom& g, int Vhp, const void* canon, int i0, int n, c
 // corners of a site (s4 = +1) share 18 matrices of level 2 and 20 of level 3:
 // 128 products and 164 links a site instead of 320 and 512 with every corner
 // on its own, which was bound by those loads (9.7 GB through L2 on 16^3 x 32,
-// 849 us, and 65 for the 32-bit and 16-bit copies; now 271 with the copies).  A block takes 16 sites, one matrix of the level per thread row
-// (16 lanes), and the levels meet in LDS (46 KB: three blocks per CU).  Each
-// corner's sums run in the same order as on its own.
+// 849 us, and 65 for the 32-bit and 16-bit copies; now 271 with the copies).
+// A block takes 16 sites, one matrix of the level per thread row (16 lanes),
+// and the levels meet in LDS (46 KB: three blocks per CU).  Each corner's
+// sums run in the same order as on its own.
 struct M3 { double2 e[9]; };
 
 __device__ __forceinline__ void m3_load(const double2* __restrict__ u, int Vp, int mu, int site,
