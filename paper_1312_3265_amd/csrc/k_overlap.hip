@@ -5,9 +5,10 @@
 // with (A^dag A)^{-1/2} replaced by the Chebyshev interpolant p of x^{-1/2} on
 // [lo, hi] (an interval containing the spectrum of A^dag A), applied to psi by
 // the three-term recurrence T_{k+1} = 2 X T_k - T_{k-1}, X = (2 A^dag A -
-// (hi + lo)) / (hi - lo): one A^dag A (two FP64 stencil launches of the
-// kernel, Gamma_55 from corners or on the fly) and one vector launch per
-// degree.  Its error in V is at most max over [lo, hi] of |x^{1/2} p(x) - 1|.
+// (hi + lo)) / (hi - lo): one A^dag A per degree, two FP64 stencil launches of
+// the kernel (Gamma_55 from corners or on the fly), the second with the
+// recurrence in its epilogue (as a launch of its own, it took a third of the
+// time of a degree on 8^3 x 16).  Its error in V is at most max over [lo, hi] of |x^{1/2} p(x) - 1|.
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -18,7 +19,7 @@ namespace lq {
 
 // FP64 fields of the staggered Wilson kernel are 3 planes of Vp complex
 // numbers; the elementwise kernels run over all 3 * Vp elements (the plane
-// padding is zero in every operand and stays zero).
+// padding is zero in every operand and stays zero; the stencils leave it).
 __global__ void __launch_bounds__(256)
 cheb_first_kernel(const double2* __restrict__ q, const double2* __restrict__ v,
                   double2* __restrict__ t, double2* __restrict__ y, double a, double b, double c0,
@@ -32,23 +33,6 @@ cheb_first_kernel(const double2* __restrict__ q, const double2* __restrict__ v,
   yv.x = c0 * vv.x + c1 * tv.x;
   yv.y = c0 * vv.y + c1 * tv.y;
   t[e] = tv;
-  y[e] = yv;
-}
-
-// t_next = 2 (a q + b t) - t_prev, written over t_prev; y += c t_next
-__global__ void __launch_bounds__(256)
-cheb_step_kernel(const double2* __restrict__ q, const double2* __restrict__ t,
-                 double2* __restrict__ tp, double2* __restrict__ y, double a, double b, double c,
-                 size_t n) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const double2 qv = q[e], tv = t[e], pv = tp[e];
-  double2 nv, yv = y[e];
-  nv.x = 2.0 * (a * qv.x + b * tv.x) - pv.x;
-  nv.y = 2.0 * (a * qv.y + b * tv.y) - pv.y;
-  yv.x += c * nv.x;
-  yv.y += c * nv.y;
-  tp[e] = nv;
   y[e] = yv;
 }
 
@@ -137,8 +121,15 @@ void overlap_apply(const lq_gauge_s* gs, const lq_overlap* ov, const void* in, v
   // t_prev starts as v: copy it so that the recurrence may overwrite it
   LQ_HIP(hipMemcpyAsync(tp, v, vec, hipMemcpyDeviceToDevice, s));
   for (int k = 2; k <= ov->degree; ++k) {
-    AdA(t, q);
-    hipLaunchKernelGGL(cheb_step_kernel, grid, blk, 0, s, q, t, tp, y, a, b, cf[k], n);
+    e.out = tmp;
+    launch_stencil(op, P64, nl, false, EPI_STORE, oa, t, e, 1, s);
+    e.cheb_t = t;
+    e.cheb_tp = tp;
+    e.cheb_y = y;
+    e.cheb_a = a;
+    e.cheb_b = b;
+    e.cheb_c = cf[k];
+    launch_stencil(op, P64, nl, true, EPI_CHEB, oa, tmp, e, 1, s);
     std::swap(t, tp);   // the new T_k is in tp's buffer
   }
   // w = A y (into q), out = (rho - m/2) (v + w) + m v (into tmp)

@@ -16,6 +16,9 @@
 //               would be.
 //   RESID       out = b - op(in), partials of ||out||^2   (FP64 true residual)
 //   LANCZOS     w = op(in) - beta_prev v_prev, partials of Re<v, w>
+//   CHEB        q = op(in) kept in registers; the three-term recurrence of the
+//               overlap operator on it: n = 2 (a q + b t) - t_prev over
+//               t_prev, y += c n
 // Partial sums are FP64, reduced in a fixed order (wavefront butterfly, then
 // waves in order), so results do not depend on scheduling.
 //
@@ -31,7 +34,8 @@
 
 namespace lq {
 
-enum Epi { EPI_STORE = 0, EPI_STORE_NORM = 1, EPI_CG_UPDATE = 2, EPI_RESID = 3, EPI_LANCZOS = 4 };
+enum Epi { EPI_STORE = 0, EPI_STORE_NORM = 1, EPI_CG_UPDATE = 2, EPI_RESID = 3, EPI_LANCZOS = 4,
+           EPI_CHEB = 5 };
 
 struct EpiArgs {
   void* out;              // output fields (STORE, STORE_NORM, RESID, LANCZOS)
@@ -54,6 +58,10 @@ struct EpiArgs {
   const double* v;        // LANCZOS: v_j
   const double* vprev;    // LANCZOS: v_{j-1}
   const double* beta_prev;// LANCZOS: device scalar beta_{j-1} (null = 0)
+  const double2* cheb_t;  // CHEB: T_{k-1}, the input of the first stencil
+  double2* cheb_tp;       // CHEB: T_{k-2}, receives T_k
+  double2* cheb_y;        // CHEB: the sum so far
+  double cheb_a, cheb_b, cheb_c;
   int rhs_per_thread;     // systems per thread (1, 2 or up to 4; FP32/Q16 CG kernels)
   int window;             // block order: > 0 window width, 0 whole range, -1/-2 system-major,
                           // -3/-4 tiled (map_block, map_block_tiled)
@@ -244,6 +252,19 @@ __device__ __forceinline__ double site_finish(const OpArgs& oa, const EpiArgs& e
       out[e] = w;
       acc += w.x * w.x + w.y * w.y;
     }
+  } else if constexpr (EPI == EPI_CHEB) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const size_t e = off + (size_t)q * Vp + i;
+      const double2 qv = o[q], tv = ea.cheb_t[e], pv = ea.cheb_tp[e];
+      double2 nv, yv = ea.cheb_y[e];
+      nv.x = 2.0 * (ea.cheb_a * qv.x + ea.cheb_b * tv.x) - pv.x;
+      nv.y = 2.0 * (ea.cheb_a * qv.y + ea.cheb_b * tv.y) - pv.y;
+      yv.x += ea.cheb_c * nv.x;
+      yv.y += ea.cheb_c * nv.y;
+      ea.cheb_tp[e] = nv;
+      ea.cheb_y[e] = yv;
+    }
   } else if constexpr (EPI == EPI_LANCZOS) {
     double2* out = (double2*)ea.out + off;
     const double2* v = (const double2*)ea.v + off;
@@ -276,7 +297,7 @@ __device__ __forceinline__ void site_epilogue(const OpArgs& oa, const EpiArgs& e
     const int k = k0 + kk;
     double acc = 0.0;
     if (valid) acc = site_finish<Op, EPI, CP>(oa, ea, k, i, o[kk], alpha[kk]);
-    if constexpr (EPI != EPI_STORE) {
+    if constexpr (EPI != EPI_STORE && EPI != EPI_CHEB) {
       const double bs = block_sum(acc, red);
       if (threadIdx.x == 0) ea.part[(size_t)k * ea.nbp + sb] = bs;
     }

@@ -92,6 +92,8 @@ static void dispatch_epi(bool dag, int epi, const OpArgs& oa, const void* in, co
         case EPI_LANCZOS: return launch_one<OpT, P, NL, true, EPI_LANCZOS>(oa, in, ea, nrhs, s);
         default: break;
       }
+      if constexpr (OpT<P, NL, true>::NC == 3)   // the overlap operator's kernels
+        if (epi == EPI_CHEB) return launch_one<OpT, P, NL, true, EPI_CHEB>(oa, in, ea, nrhs, s);
     }
   }
   throw std::runtime_error("stencil: unsupported epilogue " + std::to_string(epi) +

@@ -83,7 +83,7 @@ sw_split_kernel(const OpArgs oa, const typename Op::S* __restrict__ in, const Ep
     Op::finish(oa, f, i, k, s, o);
     acc = site_finish<Op, EPI, 0>(oa, ea, k, i, o, alpha);
   }
-  if constexpr (EPI != EPI_STORE) {
+  if constexpr (EPI != EPI_STORE && EPI != EPI_CHEB) {
     acc = wave_sum(acc);
     if (lane == 0) ea.part[(size_t)k * ea.nbp + sb] = acc;
   }
