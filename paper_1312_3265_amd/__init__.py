@@ -151,11 +151,17 @@ def _check(rc, allow_positive=False):
     return rc
 
 
+_gpu = None     # torch, once a GPU has been seen
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("the HIP library needs a GPU (torch.cuda.is_available() is False)")
-    return torch
+    global _gpu
+    if _gpu is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise RuntimeError("the HIP library needs a GPU (torch.cuda.is_available() is False)")
+        _gpu = torch
+    return _gpu
 
 
 def _stream(stream=None):
@@ -270,9 +276,10 @@ def apply(gauge, formulation, mass, psi, op=OP_M, r=1.0, g55=G55_CORNERS, precis
     nb = int(lib().lq_apply_workspace_bytes(gauge._h, formulation, g55, precision))
     ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
     d = Dirac(formulation, g55, mass, r)
+    s = stream if stream is not None else torch.cuda.current_stream()
     _check(lib().lq_apply(gauge._h, ctypes.byref(d), op, precision, links, _ptr(x), _ptr(out),
-                          _ptr(ws), nb, _stream(stream)))
-    _stream_sync(stream)
+                          _ptr(ws), nb, _stream(s)))
+    s.synchronize()
     return out
 
 
