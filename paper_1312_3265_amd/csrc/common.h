@@ -237,8 +237,12 @@ __device__ __forceinline__ int nb_bwd(const Geom& g, const Coord& c, int i, int 
 //
 // Loads and stores are raw buffer accesses: the array base is wavefront-
 // uniform (a buffer descriptor in scalar registers), the slab offset a scalar
-// offset and the per-lane part a 32-bit vector offset.  Every array a kernel
-// reads this way is smaller than 4 GiB (checked at lattice creation).
+// offset and the per-lane part a 32-bit vector offset.  An array read this way
+// has to be smaller than 4 GiB, which nothing checks: 22.3 million sites of a
+// 12-component FP64 vector, 29.8 of an 18-real FP64 link or corner, 44.7 of a
+// 12-real one or a 12-component FP32 vector, 59.6 of an 18-real FP32 link.
+// FP64 links and corners are written with 64-bit addresses (st_matrix64), and
+// the plaquette and setup kernels read them so: those hold on every lattice.
 constexpr int kBufferDword3 = 0x00020000;   // raw (untyped) buffer access on CDNA
 
 template <int BYTES>
@@ -496,16 +500,27 @@ __device__ __forceinline__ void load_link(const typename P::S* __restrict__ u, i
   ld_link_words<P, NREAL>(u, Vp, mu, site, w);
   dec_link<P, NREAL, RAW>(w, m);
 }
+// the nine slabs of an FP64 matrix at site i (18 reals)
+__host__ __device__ __forceinline__ void st_matrix64(double2* __restrict__ base, int Vp, int i,
+                                                     const double2 m[9]) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) base[(size_t)k * Vp + i] = m[k];
+}
 template <class P, int NREAL>
-__device__ __forceinline__ void store_link(typename P::S* __restrict__ u, int Vp, int mu, int site,
+__host__ __device__ __forceinline__ void store_link(typename P::S* __restrict__ u, int Vp, int mu, int site,
                                            const typename P::C m[9]) {
   constexpr int NCX = NREAL / 2;
-  constexpr int BY = NCX * (int)sizeof(typename P::S);
-  constexpr int WPC = sizeof(typename P::S) / 4;
-  uint32_t w[BY / 4];
+  if constexpr (P::id == 0) {
+    static_assert(NREAL == 18, "FP64 links are stored with 18 reals");
+    st_matrix64(u + (size_t)mu * 9 * Vp, Vp, site, m);
+  } else {
+    constexpr int BY = NCX * (int)sizeof(typename P::S);
+    constexpr int WPC = sizeof(typename P::S) / 4;
+    uint32_t w[BY / 4];
 #pragma unroll
-  for (int k = 0; k < NCX; ++k) enc_to<P>(w + k * WPC, m[k]);
-  st_rec<BY>(u + (size_t)mu * NCX * Vp, Vp, site, w);
+    for (int k = 0; k < NCX; ++k) enc_to<P>(w + k * WPC, m[k]);
+    st_rec<BY>(u + (size_t)mu * NCX * Vp, Vp, site, w);
+  }
 }
 template <class P>
 __device__ __forceinline__ void ld_corner_words(const typename P::S* __restrict__ c, int Vp,
@@ -514,14 +529,18 @@ __device__ __forceinline__ void ld_corner_words(const typename P::S* __restrict_
   ld_rec<4 * kLinkWords<P, 18>>(c + (size_t)cidx * 9 * Vp, Vp, site, w);
 }
 template <class P>
-__device__ __forceinline__ void store_corner(typename P::S* __restrict__ c, int Vp, int cidx,
+__host__ __device__ __forceinline__ void store_corner(typename P::S* __restrict__ c, int Vp, int cidx,
                                              int site, const typename P::C m[9]) {
-  constexpr int BY = 9 * (int)sizeof(typename P::S);
-  constexpr int WPC = sizeof(typename P::S) / 4;
-  uint32_t w[BY / 4];
+  if constexpr (P::id == 0) {
+    st_matrix64(c + (size_t)cidx * 9 * Vp, Vp, site, m);
+  } else {
+    constexpr int BY = 9 * (int)sizeof(typename P::S);
+    constexpr int WPC = sizeof(typename P::S) / 4;
+    uint32_t w[BY / 4];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) enc_to<P>(w + k * WPC, m[k]);
-  st_rec<BY>(c + (size_t)cidx * 9 * Vp, Vp, site, w);
+    for (int k = 0; k < 9; ++k) enc_to<P>(w + k * WPC, m[k]);
+    st_rec<BY>(c + (size_t)cidx * 9 * Vp, Vp, site, w);
+  }
 }
 
 // y = M v and y = M^dag v for a 3x3 matrix and a colour vector
