@@ -237,7 +237,7 @@ __device__ __forceinline__ int nb_bwd(const Geom& g, const Coord& c, int i, int 
 //
 // Loads and stores are raw buffer accesses: the array base is wavefront-
 // uniform (a buffer descriptor in scalar registers), the slab offset a scalar
-// offset and the per-lane part a 32-bit vector offset.  An array read this way
+// offset (of loads; see st_rec) and the per-lane part a 32-bit vector offset.  An array read this way
 // has to be smaller than 4 GiB, which nothing checks: 22.3 million sites of a
 // 12-component FP64 vector, 29.8 of an 18-real FP64 link or corner, 44.7 of a
 // 12-real one or a 12-component FP32 vector, 59.6 of an 18-real FP32 link.
@@ -287,6 +287,13 @@ __device__ __forceinline__ void ld_rec(const void* __restrict__ base, int Vp, in
   }
 }
 
+// Stores keep the whole offset in the vector register: a 128-bit store reads
+// its data for a few cycles after it is issued, and the compiler keeps the
+// next two cycles' instructions from writing those registers only where the
+// store has no scalar offset (with one it takes the registers as free at
+// once, which on gfx950 they are not).  With scalar offsets the CG update of
+// two even-odd FP32 systems per thread stored, in four lanes of sixteen, the
+// doubles that the next instruction wrote over the last slab of x.
 template <int BYTES, int CP = 0>
 __device__ __forceinline__ void st_rec(void* __restrict__ base, int Vp, int i,
                                        const uint32_t w[Rec<BYTES>::W], uint32_t lo = 0) {
@@ -298,15 +305,16 @@ __device__ __forceinline__ void st_rec(void* __restrict__ base, int Vp, int i,
 #pragma unroll
   for (int j = 0; j < R::A; ++j) {
     u4 v = {w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
-    __builtin_amdgcn_raw_buffer_store_b128(v, rs, lo + ui * 16u, (uint32_t)j * vp * 16u, CP);
+    __builtin_amdgcn_raw_buffer_store_b128(v, rs, lo + ((uint32_t)j * vp + ui) * 16u, 0, CP);
   }
   if constexpr (R::B) {
     u2 v = {w[4 * R::A], w[4 * R::A + 1]};
-    __builtin_amdgcn_raw_buffer_store_b64(v, rs, lo + ui * 8u, (uint32_t)R::A * vp * 16u, CP);
+    __builtin_amdgcn_raw_buffer_store_b64(v, rs, lo + (uint32_t)R::A * vp * 16u + ui * 8u, 0, CP);
   }
   if constexpr (R::C) {
-    __builtin_amdgcn_raw_buffer_store_b32(w[R::W - 1], rs, lo + ui * 4u,
-                                          (uint32_t)R::A * vp * 16u + (uint32_t)R::B * vp * 8u, CP);
+    __builtin_amdgcn_raw_buffer_store_b32(
+        w[R::W - 1], rs,
+        lo + (uint32_t)R::A * vp * 16u + (uint32_t)R::B * vp * 8u + ui * 4u, 0, CP);
   }
 }
 
@@ -325,8 +333,8 @@ __device__ __forceinline__ void st_c64(void* __restrict__ base, int Vp, int i, i
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   u4 v;
   __builtin_memcpy(&v, &z, 16);
-  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc(base), (uint32_t)i * 16u,
-                                         (uint32_t)q * (uint32_t)Vp * 16u, CP);
+  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc(base),
+                                         ((uint32_t)q * (uint32_t)Vp + (uint32_t)i) * 16u, 0, CP);
 }
 
 // Storage words <-> complex values of a policy
