@@ -100,17 +100,26 @@ static void dispatch_epi(bool dag, int epi, const OpArgs& oa, const void* in, co
                            " for precision " + std::to_string(P::id));
 }
 
+[[noreturn]] inline void unsupported_storage(int prec, int nl) {
+  throw std::runtime_error("stencil: unsupported precision/link storage " + std::to_string(prec) +
+                           "/" + std::to_string(nl));
+}
+
+template <template <class, int, bool> class OpT, class P>
+static void dispatch_links(int nl, bool dag, int epi, const OpArgs& oa, const void* in,
+                           const EpiArgs& ea, int nrhs, hipStream_t s) {
+  if (nl == 18) return dispatch_epi<OpT, P, 18>(dag, epi, oa, in, ea, nrhs, s);
+  if (nl == 12) return dispatch_epi<OpT, P, 12>(dag, epi, oa, in, ea, nrhs, s);
+  unsupported_storage(P::id, nl);
+}
+
 template <template <class, int, bool> class OpT>
 static void dispatch_prec(int prec, int nl, bool dag, int epi, const OpArgs& oa, const void* in,
                           const EpiArgs& ea, int nrhs, hipStream_t s) {
-  if (prec == P64 && nl == 18) return dispatch_epi<OpT, F64, 18>(dag, epi, oa, in, ea, nrhs, s);
-  if (prec == P64 && nl == 12) return dispatch_epi<OpT, F64, 12>(dag, epi, oa, in, ea, nrhs, s);
-  if (prec == P32 && nl == 18) return dispatch_epi<OpT, F32, 18>(dag, epi, oa, in, ea, nrhs, s);
-  if (prec == P32 && nl == 12) return dispatch_epi<OpT, F32, 12>(dag, epi, oa, in, ea, nrhs, s);
-  if (prec == P16 && nl == 12) return dispatch_epi<OpT, Q16, 12>(dag, epi, oa, in, ea, nrhs, s);
-  if (prec == P16 && nl == 18) return dispatch_epi<OpT, Q16, 18>(dag, epi, oa, in, ea, nrhs, s);
-  throw std::runtime_error("stencil: unsupported precision/link storage " + std::to_string(prec) +
-                           "/" + std::to_string(nl));
+  if (prec == P64) return dispatch_links<OpT, F64>(nl, dag, epi, oa, in, ea, nrhs, s);
+  if (prec == P32) return dispatch_links<OpT, F32>(nl, dag, epi, oa, in, ea, nrhs, s);
+  if (prec == P16) return dispatch_links<OpT, Q16>(nl, dag, epi, oa, in, ea, nrhs, s);
+  unsupported_storage(prec, nl);
 }
 
 }  // namespace lq
