@@ -284,7 +284,7 @@ struct WilsonOp {
       } else if constexpr (P::id != 0) {
         using Hops = WilsonHops<P, NL, DAG, K, false>;
         typename Hops::Words w[Hops::AHEAD + 1];
-        R one[K];
+        R one[K] = {};   // the even-odd factors: not used
         Hops::run(g, a.links, a.links, in0, rstride, c, i, i, act, one, w, acc);
       } else {
 #pragma unroll 1

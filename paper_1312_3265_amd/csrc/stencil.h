@@ -153,6 +153,21 @@ __device__ __forceinline__ bool slot_active(const SlotState* st, int k, int mode
 // once per site for all K.  Each system keeps its own alpha, state and
 // partial sums, so the result of a system does not depend on K or on the
 // other systems.
+// kComputesAll: site_multi<K> runs the arithmetic of all K systems, whichever
+// are active (no branch between a term's systems).  A group with one active
+// system -- the others of a pool's slots empty, or of a batch finished, or the
+// last group of an odd number -- then takes the one-system path: 16-bit, groups
+// of two with one active, 24^3 x 48, M p and the CG update: Wilson 59 + 89 us
+// computing both, 39 + 75 so; even-odd 64 + 75, 44 + 58 (FP32 Wilson 91 + 131,
+// 83 + 123; staggered groups of four 110 + 138, 69 + 114).
+template <class Op, int K> constexpr bool kComputesAll = false;
+template <class P, int NL, bool DAG>
+constexpr bool kComputesAll<WilsonOpR1<P, NL, DAG>, 2> = P::id != 0;
+template <class P, int NL, bool DAG>
+constexpr bool kComputesAll<WilsonEOOp<P, NL, DAG>, 2> = P::id != 0;
+template <class P, int NL, bool DAG, int K>
+constexpr bool kComputesAll<SWCornerOp<P, NL, DAG>, K> = K > 1;
+
 template <class Op, int K>
 constexpr int stencil_waves() { return (Op::NC == 12 ? K >= 2 : K >= 3) ? 3 : Op::kWaves; }
 
@@ -304,14 +319,25 @@ __device__ __forceinline__ void site_epilogue(const OpArgs& oa, const EpiArgs& e
   }
 }
 
+// CG_UPDATE: alpha of system k from the partials of ||t||^2; the block of site
+// block 0 records it, and a breakdown.
+__device__ __forceinline__ double cg_alpha(const EpiArgs& ea, int V, int k, int sb, double* red) {
+  const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red, partials_per(V));
+  const double rho = ea.st[k].rho[ea.par];
+  const double alpha = (tt > 0.0 && isfinite(tt) && isfinite(rho)) ? rho / tt : 0.0;
+  if (sb == 0 && threadIdx.x == 0) {
+    if (!(tt > 0.0 && isfinite(tt))) ea.st[k].flags |= 1;
+    ea.st[k].alpha[ea.q4] = alpha;   // read on the group's last iteration
+  }
+  return alpha;
+}
+
 template <class Op, int EPI, int K, int CP>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(stencil_waves<Op, K>(), 8)))
 stencil_kernel(const OpArgs oa, const typename Op::S* __restrict__ in, const EpiArgs ea,
                int ngroups, int nrhs) {
   using P_C = typename Op::C;
-  using R = typename Op::R;
-  using S = typename Op::S;
   constexpr int NC = Op::NC;
   __shared__ double red[16];
   int sb, kg;
@@ -333,20 +359,26 @@ stencil_kernel(const OpArgs oa, const typename Op::S* __restrict__ in, const Epi
   const bool valid = i < oa.g.V;
   const size_t rstride = (size_t)field_planes<typename Op::Pol>(NC) * Vp;
 
+  if constexpr (kComputesAll<Op, K>) {
+    if ((act & (act - 1)) == 0) {   // uniform over the block
+      const int k = k0 + __ffs(act) - 1;
+      double alpha[1];
+      if constexpr (EPI == EPI_CG_UPDATE) alpha[0] = cg_alpha(ea, oa.g.V, k, sb, red);
+      P_C o[1][NC];
+      if (valid)
+        Op::template site_multi<1>(oa, in + (size_t)k * rstride, rstride, i, k, 1u, o);
+      site_epilogue<Op, EPI, 1, CP>(oa, ea, k, 1u, i, valid, sb, o, alpha, red);
+      return;
+    }
+  }
+
   double alpha[K];
   if constexpr (EPI == EPI_CG_UPDATE) {
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) {
       alpha[kk] = 0.0;
       if (!((act >> kk) & 1)) continue;
-      const int k = k0 + kk;
-      const double tt = sum_partials(ea.part_in + (size_t)k * ea.nbp, ea.nbp, red, partials_per(oa.g.V));
-      const double rho = ea.st[k].rho[ea.par];
-      alpha[kk] = (tt > 0.0 && isfinite(tt) && isfinite(rho)) ? rho / tt : 0.0;
-      if (sb == 0 && threadIdx.x == 0) {
-        if (!(tt > 0.0 && isfinite(tt))) ea.st[k].flags |= 1;
-        ea.st[k].alpha[ea.q4] = alpha[kk];   // read on the group's last iteration
-      }
+      alpha[kk] = cg_alpha(ea, oa.g.V, k0 + kk, sb, red);
     }
   }
 
