@@ -553,19 +553,37 @@ void Engine::enqueue_iterations(int n, hipStream_t s) {
   }
 }
 
+// Block order of the FP64 stencils of a reliable update of `selected` systems:
+// two site blocks for all of them before the next two (2), so that their links
+// and corners come from L2, or whole sweeps (0), which keep more of a system's
+// own vectors there.  An XCD's share of the matrices is read again by every
+// system but the first unless it stays in the XCD's 4 MiB of L2: the first
+// order pays where that share does not fit beside the vectors and the reads
+// saved outweigh the vectors' (unpreconditioned Wilson has the most vector
+// bytes per link).  M, whole sweeps against pairs of blocks, in us: staggered
+// 16^3 x 32 (24 MiB per XCD) one system 55, 61, two 113, 75, nine 548, 215;
+// 8^2 x 16^2 (3 MiB) two 9.7, 12.6, four 17.0, 15.0, nine 34, 28; even-odd
+// 16^3 x 32 (6 MiB) one 35, 37, two 68, 58, nine 350, 249, 12^3 x 16 (1.3 MiB)
+// nine 46, 54; Wilson 24^3 x 48 (30 MiB) one 184, 227, two 358, 383, three 532,
+// 531, nine 1577, 1351, 8^2 x 16^2 (0.8 MiB) nine 26, 34.
+static int shared_window(int op, int nl, int V, int selected) {
+  const double share = (4 * nl / 2 + (op == OP_SW_CORNERS ? 8 * 9 : 0)) * 16.0 * V / 8;
+  const double mib = 1 << 20;
+  if (selected < (op == OP_WILSON ? 3 : 2) || share < 2 * mib) return 0;
+  return (selected - 1) * share >= 6 * mib ? 2 : 0;
+}
+
 void Engine::enqueue_reliable_update(hipStream_t s) {
   const Geom& g = vg;
+  int selected = 0;
+  for (int k = 0; k < nslots; ++k) selected += hmask[k] != 0;
   const int nl64 = gauge->fp64_links();
   LQ_HIP(hipMemcpyAsync(mask, hmask, sizeof(int) * nslots, hipMemcpyHostToDevice, s));
   launch_ru_accumulate(prec_lo, nc, g, st, mask, (double*)xhi, xlo, ring(), nbp, 0, nslots, s);
   EpiArgs e = epi_base();
   e.state_mode = 2;
   e.ru_mask = mask;
-  // several systems: two site blocks for all of them before the next two, so
-  // that their FP64 links and corners come from L2 (staggered Wilson M,
-  // nine systems: 558 us in whole sweeps, 224 us so on 16^3 x 32, 3.33 and
-  // 1.40 ms on 24^3 x 48; one system 55 and 61 us)
-  e.window = nslots > 1 ? 2 : 0;
+  e.window = shared_window(op, nl64, gauge->g.V, selected);
   EpiArgs f = epi_base();
   f.state_mode = 2;
   f.ru_mask = mask;
