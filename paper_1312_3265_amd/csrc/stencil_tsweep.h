@@ -68,14 +68,22 @@ wilson_tsweep_kernel(const OpArgs oa, const double2* __restrict__ in, const EpiA
   const int P = plane >> 8, NT = g.L[3] / T;
   const int per = P * g.L[2] * NT;       // blocks per system (a multiple of 8)
   // block b runs on XCD b % 8 as its (b / 8)-th block; XCD x takes the x-th
-  // eighth of the (t-chunk, z, slab) blocks, slabs innermost, each for all
-  // systems in turn: a block's links then come from that XCD's L2 for every
-  // system but the first (system-major, each system fetched them again:
-  // M of 5, 8 and 36 systems on 16^3 x 32 126, 201 and 882 us, now 104, 168
-  // and 813; M^dag with the CG update 208, 306 and 1308, now 190, 293, 1375)
+  // eighth of the (t-chunk, z, slab) blocks, slabs innermost, each for G
+  // systems in turn, group after group: a block's links then come from that
+  // XCD's L2 for every system of a group but the first.  G = all systems
+  // (system-major, each system fetched the links again: M of 5, 8 and 36
+  // systems on 16^3 x 32 125, 199 and 878 us, so 104, 167 and 799), but four
+  // with the CG update, whose r, x and p push the links out of L2 when many
+  // systems take turns (system-major, fours, all: four systems 158, 144, 144,
+  // eight 306, 295, 294, 36 systems 1307, 1278, 1384; on 32^3 x 64 four 2446,
+  // 2453, 2453, eight 4994, 4976, 5661)
   const int b = blockIdx.x, xcd = b & 7, kk = b >> 3;
-  const int kr = kk % nrhs;
-  int rem = xcd * (per >> 3) + kk / nrhs;
+  const int G = EPI == EPI_CG_UPDATE ? 4 : nrhs;
+  const int g0 = kk / ((per >> 3) * G) * G;          // the group's first system
+  const int width = min(G, nrhs - g0);
+  const int kg = kk - g0 * (per >> 3);
+  const int kr = g0 + kg % width;
+  int rem = xcd * (per >> 3) + kg / width;
   const int p = rem % P;
   rem /= P;
   const int z = rem % g.L[2];
