@@ -287,7 +287,9 @@ int lq_schur_apply(const lq_gauge* g, const lq_dirac* d, int32_t dagger, int32_t
  * LQ_FEAT_EO), each a pair of half-lattice launches: t = M^ p with ||t||^2,
  * and M^dag t fused with the CG update; the average is per pair.  rhs_per_thread (1, 2, 4;
  * FP32/Q16 only) is the number of systems each thread serves, the choice the
- * solvers' autotuner makes per batch; 8 selects the lanes stencil (kernels 0-2,
+ * solvers' autotuner makes per batch (small staggered Wilson batches, whose
+ * sites are split over wavefronts, run one whatever it is: up to 16384 sites
+ * and 32768 sites of all systems together, 65536 with 16-bit storage); 8 selects the lanes stencil (kernels 0-2,
  * Wilson, r = 1, 18-real links: four systems across the lanes of each site,
  * the link products on the matrix cores, results bitwise those of 1); window, the autotuner's other choice,
  * is the block order: w > 0 sweeps windows of w site blocks per XCD over all
@@ -295,8 +297,9 @@ int lq_schur_apply(const lq_gauge* g, const lq_dirac* d, int32_t dagger, int32_t
  * gives each XCD a contiguous eighth of the system-major (system, site)
  * order, -2 the same with every other system swept backwards; -3 and -4 tile
  * each XCD's eighth of the t range in chunks of two z-planes with t inner,
- * systems outermost (-3) or innermost (-4) -- on lattices with whole x-y
- * planes of 256-site blocks, L4 % 8 == 0 and even L3; elsewhere they act as 0.
+ * systems outermost (-3) or innermost (-4) -- on lattices of more than 16384
+ * sites (smaller ones have 64-site blocks) with whole x-y planes of 256-site
+ * blocks, L4 % 8 == 0 and even L3; elsewhere they act as 0.
  * -11, -12, -13 (16-bit Wilson, r = 1, one system per thread, kernels 0-2):
  * each block sweeps one system's 256-site slab through T = 2, 4, 8 t-slices,
  * the diagonal and the x-y neighbours from LDS (x-y planes of exactly 256

@@ -192,7 +192,7 @@ struct Engine {
   void eo_form(int par, int form, bool dag, const void* diag, const void* in, EpiArgs e, int epi,
                int nrhs, hipStream_t s) const;
   EpiArgs epi_base() const;
-  void enqueue_iterations(int n, hipStream_t s);
+  void enqueue_iterations(int n, int active, hipStream_t s);
   void enqueue_reliable_update(hipStream_t s);
   void poll(hipStream_t s);
   bool select_updates();

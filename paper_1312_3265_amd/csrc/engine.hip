@@ -160,7 +160,7 @@ std::string tune_key(const Geom& g, int op, int prec, int nl, int nslots) {
   LQ_HIP(hipGetDevice(&dev));
   LQ_HIP(hipGetDeviceProperties(&prop, dev));
   std::ostringstream key;
-  key << "v16:" << prop.gcnArchName << ":" << g.L[0] << "x" << g.L[1] << "x" << g.L[2] << "x" << g.L[3]
+  key << "v17:" << prop.gcnArchName << ":" << g.L[0] << "x" << g.L[1] << "x" << g.L[2] << "x" << g.L[3]
       << ":op" << op << ":p" << prec << ":l" << nl << ":n" << nslots;
   std::string k = key.str();
   for (auto& ch : k) if (ch == ' ') ch = '_';
@@ -224,10 +224,14 @@ void Engine::tune(hipStream_t s) {
   // Every candidate is timed twice, in two passes of opposite order, and
   // keeps its faster time, so that work of other streams running meanwhile
   // (a caller's concurrent batches) is less likely to decide the choice.
+  // Not candidates, the same launch as another one: the tiled orders (-3, -4)
+  // on fields of 64-site blocks (order 0 there), and several systems per thread
+  // where the staggered stencil runs as the split kernel.
   std::vector<std::pair<int, int>> cand;
   for (int kk : {1, 2, 4})
-    if (kk <= nslots)
-      for (int w : {1, 2, 4, 0, -3, -4}) cand.push_back({kk, w});
+    if (kk <= nslots && (kk == 1 || op != OP_SW_CORNERS || !sw_split_fits(prec_lo, vg.V, nslots)))
+      for (int w : {1, 2, 4, 0, -3, -4})
+        if (w >= 0 || block_of(vg.V) != 64) cand.push_back({kk, w});
   // the t-sweeping Wilson stencils (16-bit, one system per thread; bitwise
   // the same results as the orders above)
   if (op == OP_WILSON && r == 1.0 && prec_lo == P16)
@@ -520,7 +524,7 @@ void Engine::load(int slot, const void* chi, double mass, double tol, int maxite
   LQ_HIP(hipStreamSynchronize(s));
 }
 
-void Engine::enqueue_iterations(int n, hipStream_t s) {
+void Engine::enqueue_iterations(int n, int active, hipStream_t s) {
   // n is a multiple of four (so of the group size): a chunk starts and ends
   // with p_k in ring buffer 0; x advances on the last iteration of each
   // group, by the group's steps
@@ -531,6 +535,7 @@ void Engine::enqueue_iterations(int n, hipStream_t s) {
     void* pn = rg.p[(q + 1) % group];   // receives p_{k+1}; its old direction is already in x
     EpiArgs e = epi_base();
     e.par = par;
+    e.active = active;
     e.state_mode = 1;
     e.out = t;
     e.part = part_t;
@@ -541,6 +546,7 @@ void Engine::enqueue_iterations(int n, hipStream_t s) {
     f.rhs_per_thread = rhs_per_thread;
     f.window = window;
     f.par = par;
+    f.active = active;
     f.q4 = q;
     f.xstep = q == group - 1 ? group : 0;
     f.state_mode = 1;
@@ -584,10 +590,12 @@ void Engine::enqueue_reliable_update(hipStream_t s) {
   e.state_mode = 2;
   e.ru_mask = mask;
   e.window = shared_window(op, nl64, gauge->g.V, selected);
+  e.active = selected;
   EpiArgs f = epi_base();
   f.state_mode = 2;
   f.ru_mask = mask;
   f.window = e.window;
+  f.active = selected;
   f.out = rhi;
   f.part = part_u;
   if (eo) {
@@ -657,7 +665,7 @@ void Engine::step(int iters, hipStream_t s) {
         if (graph) { (void)hipGraphDestroy(graph); graph = nullptr; }
         LQ_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
         try {
-          enqueue_iterations(n, s);
+          enqueue_iterations(n, nslots, s);   // replayed with any number running
         } catch (...) {
           hipGraph_t tmp;
           (void)hipStreamEndCapture(s, &tmp);
@@ -672,7 +680,7 @@ void Engine::step(int iters, hipStream_t s) {
       LQ_HIP(hipGraphLaunch(gexec, s));
       graphed = true;
     }
-    if (!graphed) enqueue_iterations(n, s);
+    if (!graphed) enqueue_iterations(n, running(), s);
     check_launch();
     done += n;
     poll(s);

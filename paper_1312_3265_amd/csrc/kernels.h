@@ -18,6 +18,23 @@ struct PRing {
   void* p[4];
 };
 
+// Whether the staggered corner stencil splits a site's terms over the
+// wavefronts of its block (stencil_swsplit.h) for nrhs systems of V sites:
+// fields of one-wavefront blocks, where the launch's blocks are resident
+// together -- two a compute unit in FP64 (their LDS) and FP32 (registers),
+// four in 16 bits.  Past that the one-thread form (with systems sharing the
+// matrices of a thread) is ahead.  M p and the CG update together, split
+// against the best one-thread form, in us: FP64 8^4 eight systems (512 blocks)
+// 16 and 20, nine 22 and 20, 16^2 x 8^2 one (256) 20 and 30, two 32 and 31,
+// nine 121 and 64, 36 457 and 306; FP32 12^2 x 8^2 three (432) 13 and 14, four
+// 17 and 15, 16^2 x 8^2 36 systems 154 and 97; 16 bits 8^4 eighteen (1152) 21
+// and 23, 24 (1536) 24 and 23, 16^2 x 8^2 three (768) 16 and 17, 36 115 and 70.
+// The two forms add the terms in the same order, so the choice does not change
+// a system's bits.
+inline bool sw_split_fits(int prec, int V, int nrhs) {
+  return block_of(V) == 64 && (long long)nbp_of(V) * nrhs <= (prec == P16 ? 1024 : 512);
+}
+
 // ---- stencils: op = OpKind, prec = Prec, nl = 18/12 link reals
 void launch_stencil(int op, int prec, int nl, bool dag, int epi, const OpArgs& oa,
                     const void* in, const EpiArgs& ea, int nrhs, hipStream_t s);

@@ -65,6 +65,8 @@ struct EpiArgs {
   int rhs_per_thread;     // systems per thread (1, 2 or up to 4; FP32/Q16 CG kernels)
   int window;             // block order: > 0 window width, 0 whole range, -1/-2 system-major,
                           // -3/-4 tiled (map_block, map_block_tiled)
+  int active;             // systems that the launch is expected to compute (0: all); the
+                          // others' blocks exit at once
   int stream;             // CG_UPDATE, FP32/Q16: 1 = r, p, x loaded and stored non-temporal
 };
 

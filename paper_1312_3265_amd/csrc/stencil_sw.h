@@ -13,15 +13,16 @@ namespace lq {
 template <class P, int NL, bool DAG>
 constexpr bool kThirds<SWCornerOp<P, NL, DAG>> = true;
 
-// Lattices of one-wavefront site blocks take the split kernel, with one system
-// per thread.  The choice depends on the lattice alone, so a system's result
-// depends neither on its batch nor on the launch configuration.
+// The split kernel (one system per thread) where sw_split_fits the systems that
+// are active (a pool of nine on 8^2 x 16^2, 16-bit, one slot running: 5.3 ms per
+// solve, 6.4 by the number of slots).
 template <class P, int NL, bool DAG, int EPI>
 struct OtherKernel<SWCornerOp<P, NL, DAG>, EPI> {
   using Op = SWCornerOp<P, NL, DAG>;
   static bool launch(const OpArgs& oa, const void* in, const EpiArgs& ea, int nrhs,
                      hipStream_t s) {
-    if (block_of(oa.g.V) != 64 || nrhs < 1) return false;
+    const int active = ea.active > 0 && ea.active < nrhs ? ea.active : nrhs;
+    if (nrhs < 1 || !sw_split_fits(P::id, oa.g.V, active)) return false;
     hipLaunchKernelGGL((sw_split_kernel<Op, EPI>), dim3(ea.nbp * nrhs), dim3(64 * Op::kGroups), 0,
                        s, oa, (const typename Op::S*)in, ea, nrhs);
     return true;

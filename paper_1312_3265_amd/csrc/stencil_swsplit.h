@@ -4,14 +4,11 @@
 // are added there in the order of the one-thread form, so the result is the
 // same to the bit; wavefront 0 runs the epilogue.
 //
-// For lattices that leave the chip idle (blocks of 64 sites, block_of): with
-// one thread per site a system of 8^3 x 16 has 128 wavefronts on 1024 SIMDs,
-// and each waits for its 24 matrices one after another.  FP64 t = M p, one
-// system, against the one-thread kernel in blocks of 256 before its loads were
-// grouped: 4^4 19 -> 6 us, 8^3 x 16 22 -> 6, 8^2 x 16^2 27 -> 7; nine systems
-// 46 -> 33 there.  On the next larger lattices (12^4 and up) batches lose what
-// single systems gain (nine systems 48 -> 82 us), and the one-thread form
-// stays.
+// For launches that leave the chip idle (sw_split_fits): with one thread per
+// site a system of 8^3 x 16 has 128 wavefronts on 1024 SIMDs, and each waits
+// for its 24 matrices one after another.  FP64 t = M p, one system, against
+// the one-thread kernel in blocks of 256 before its loads were grouped: 4^4
+// 19 -> 6 us, 8^3 x 16 22 -> 6, 8^2 x 16^2 27 -> 7.
 #pragma once
 
 #include "stencil.h"

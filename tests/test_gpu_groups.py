@@ -1,5 +1,5 @@
-"""Batches whose groups of systems per thread are full, partial or have one active system (needs an
-MI355X).
+"""Batches whose groups of systems per thread are full, partial or have one active system, and
+staggered batches on either side of the line between the stencil's two forms (needs an MI355X).
 
 Above 16384 sites the stencils run in blocks of 256 sites with the systems-per-thread count and the
 block order that LQ_LAUNCH asks for.  16 x 16 x 8 x 16 has whole x-y planes of site blocks, so the
@@ -101,3 +101,15 @@ def test_every_even_odd_group_and_order_is_bitwise_single_systems(dims, precisio
     blocks of 256."""
     _schedules(dims, W, precision, 1, 5, [(K, w) for K in (1, 2, 4) for w in (0, 1, 4, -1)],
                monkeypatch)
+
+
+@pytest.mark.parametrize("precision,n", [(lq.F64, 2), (lq.F64, 3), (lq.F32, 2), (lq.F32, 3),
+                                         (lq.Q16, 4), (lq.Q16, 5)])
+def test_split_and_one_thread_staggered_stencils_are_bitwise_equal(precision, n, monkeypatch):
+    """Up to 16384 sites the staggered stencil splits a site's terms over wavefronts while the
+    launch has at most 512 blocks of 64 sites (16-bit 1024), and keeps one thread per site beyond:
+    the systems of a batch on either side of that line have the bits of one system, which is
+    always split."""
+    dims = (16, 16, 8, 8)
+    launches = [(1, 0), (1, 2)] + ([] if precision == lq.F64 else [(2, 0), (4, 2)])
+    _schedules(dims, SW, precision, 0, n, launches, monkeypatch)
