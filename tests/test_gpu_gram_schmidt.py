@@ -34,3 +34,14 @@ def test_lanczos_across_the_tile_changes(dims, formulation, steps):
     np.testing.assert_allclose(res["beta"][:29], b[:29], rtol=1e-10)
     assert abs(res["lmin"] - lo) <= 1e-11 * hi
     assert abs(res["lmax"] - hi) <= 1e-11 * hi
+
+
+@pytest.mark.parametrize("dims,formulation,steps", [
+    ((6, 6, 6, 6), synth.WILSON, 12),      # 1296 sites: a ragged block of 64
+    ((6, 6, 8, 10), synth.WILSON, 40),     # 552 tiles of 64 elements on 512 blocks
+    ((6, 6, 8, 10), synth.WILSON, 70),     # 1104 tiles of 32
+])
+def test_lanczos_with_more_than_one_tile_per_block(dims, formulation, steps):
+    """Blocks that take a second tile use the other half of the double-buffered LDS; same bounds as
+    above."""
+    test_lanczos_across_the_tile_changes(dims, formulation, steps)
