@@ -53,11 +53,11 @@ static bool try_tsweep(bool dag, int epi, const OpArgs& oa, const void* in, cons
 }
 
 // Launches the 16-bit t-sweep; false (nothing launched) where fewer than four
-// of its blocks fit on a compute unit.  Wrong results were seen in such
-// launches: with FP32 storage (three blocks per CU), and with the 16-bit
-// kernel's LDS padded to 49 or 60 KB (three or two blocks), in the systems
-// whose blocks have indices past the first 256; padded to 33 or 38 KB (four
-// blocks) it stayed bitwise exact.  The cause was not found.
+// of its blocks fit on a compute unit, which it was not tuned for.  (With FP32
+// storage, three blocks per CU, it gave wrong results while the record stores
+// had scalar offsets: its CG update overwrote the data of a 128-bit store in
+// the next cycle, see st_rec.  With the stores as they are now it is bitwise
+// exact there too.)
 template <class P, int NL, bool DAG, int EPI, int CPL, bool XY>
 static bool launch_tsweep_lo(const OpArgs& oa, const void* in, const EpiArgs& ea, int nrhs, int T,
                              hipStream_t s) {
@@ -113,8 +113,7 @@ void launch_stencil_wilson(int prec, int nl, bool dag, int epi, const OpArgs& oa
                  : try_tsweep<18>(dag, epi, oa, in, ea, nrhs, s))
       return;
   }
-  // 16-bit storage only: with FP32 storage the kernel fits three blocks per
-  // CU and gave wrong results (launch_tsweep_lo), so FP32 keeps stencil_kernel
+  // 16-bit storage only: the FP32 form (three blocks per CU) is not built
   if (oa.r == 1.0 && prec == P16 && ea.rhs_per_thread <= 1 && ea.window <= -11) {
     if (nl == 12 ? try_tsweep_lo<Q16, 12>(dag, epi, oa, in, ea, nrhs, s)
                  : try_tsweep_lo<Q16, 18>(dag, epi, oa, in, ea, nrhs, s))
