@@ -196,7 +196,12 @@ const char* lq_last_error(void);
 const char* lq_version(void);
 
 /* --------------------------------------------------------------- lattice
- * dims: 4 lattice extents, each even and >= 4, volume < 2^28.
+ * dims: 4 lattice extents, each even and >= 4, volume < 2^28.  A gauge field
+ * and its plaquette work on all of them; an operator's calls fail with
+ * LQ_ERR_ARG where one of its arrays (a vector field, one direction's links,
+ * one corner's matrices) is 4 GiB or more: from 22.3 million sites for FP64
+ * Wilson, 29.8 for FP64 staggered Wilson from corners, 44.7 for FP32 Wilson
+ * and for FP64 Gamma_55 on the fly with SU(3) links.
  * bc:   4 fermion boundary signs, each +1 or -1 (NULL = all +1).  */
 int lq_lattice_create(const int32_t dims[4], const int32_t bc[4], lq_lattice** out);
 void lq_lattice_destroy(lq_lattice* lat);

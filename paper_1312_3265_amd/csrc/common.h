@@ -237,12 +237,13 @@ __device__ __forceinline__ int nb_bwd(const Geom& g, const Coord& c, int i, int 
 //
 // Loads and stores are raw buffer accesses: the array base is wavefront-
 // uniform (a buffer descriptor in scalar registers), the slab offset a scalar
-// offset (of loads; see st_rec) and the per-lane part a 32-bit vector offset.  An array read this way
-// has to be smaller than 4 GiB, which nothing checks: 22.3 million sites of a
+// offset (of loads; see st_rec) and the per-lane part a 32-bit vector offset.
+// An array read this way has to be smaller than 4 GiB: 22.3 million sites of a
 // 12-component FP64 vector, 29.8 of an 18-real FP64 link or corner, 44.7 of a
-// 12-real one or a 12-component FP32 vector, 59.6 of an 18-real FP32 link.
-// FP64 links and corners are written with 64-bit addresses (st_matrix64), and
-// the plaquette and setup kernels read them so: those hold on every lattice.
+// 12-real one or a 12-component FP32 vector, 59.6 of an 18-real FP32 link
+// (launch_stencil refuses more).  FP64 links and corners are written with
+// 64-bit addresses (st_matrix64), and the plaquette and setup kernels read
+// them so: those hold on every lattice.
 constexpr int kBufferDword3 = 0x00020000;   // raw (untyped) buffer access on CDNA
 
 template <int BYTES>

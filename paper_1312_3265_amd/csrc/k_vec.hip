@@ -29,6 +29,12 @@ void launch_stencil_wilson_eo(int, int, bool, int, const OpArgs&, const void*, c
 
 void launch_stencil(int op, int prec, int nl, bool dag, int epi, const OpArgs& oa, const void* in,
                     const EpiArgs& ea, int nrhs, hipStream_t s) {
+  // past 4 GiB the 32-bit offsets of the records wrap or leave the range that
+  // the loads check: results were silently wrong there
+  const uint64_t bytes = (uint64_t)widest_record(op, prec, nl) * (uint32_t)oa.g.Vp;
+  if (bytes > 0xffffffffull)
+    throw std::runtime_error("lattice too large for this operator and storage: one array takes " +
+                             std::to_string(bytes) + " bytes, the stencils address 4 GiB");
   switch (op) {
     case OP_WILSON: return launch_stencil_wilson(prec, nl, dag, epi, oa, in, ea, nrhs, s);
     case OP_SW_CORNERS: return launch_stencil_sw(prec, nl, dag, epi, oa, in, ea, nrhs, s);

@@ -1,6 +1,8 @@
 // Host-side launch interface of the kernels (one translation unit per group).
 #pragma once
 
+#include <algorithm>
+
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -33,6 +35,16 @@ struct PRing {
 // a system's bits.
 inline bool sw_split_fits(int prec, int V, int nrhs) {
   return block_of(V) == 64 && (long long)nbp_of(V) * nrhs <= (prec == P16 ? 1024 : 512);
+}
+
+// Bytes per site of the widest array that a stencil addresses from one base:
+// a vector field, one direction's links or one corner's matrices.
+inline int widest_record(int op, int prec, int nl) {
+  const int z = prec == P64 ? 16 : prec == P32 ? 8 : 4;   // a complex number
+  const int nc = op == OP_SW_CORNERS || op == OP_SW_OTF ? 3 : 12;
+  const int vec = (nc + (prec == P16)) * z, link = nl / 2 * z;
+  const int corner = op == OP_SW_CORNERS ? 9 * z : 0;
+  return std::max(std::max(vec, link), corner);
 }
 
 // ---- stencils: op = OpKind, prec = Prec, nl = 18/12 link reals
